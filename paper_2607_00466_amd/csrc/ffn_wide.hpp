@@ -1,0 +1,38 @@
+// The expert FFN's kernel for batches whose buckets are large.
+#pragma once
+
+#include "ffn_common.hpp"
+
+namespace eldr {
+
+constexpr int kWideTokens = 128;  // tokens of one item
+
+// Items an expert's rows make for one token group: 128 rows of W1 and of W3
+// (up) or 256 rows of W2 (down) each.
+template <int MODE>
+constexpr int wide_tiles(int rows) {
+  return MODE == kUp ? (rows + 127) / 128 : (rows + 255) / 256;
+}
+
+// Whether the wide kernel runs a projection of a batch of T > 64 tokens.  Its
+// items are twice as long as the small-batch kernel's, so there must be enough
+// of them to give every CU one: with E experts and T K / 128 further token
+// groups about 300 (measured: 312 items +4%, 330 items +15%, but 280 items
+// -6% and 171 items -14%).  With bf16 weights the buckets must also average 16
+// tokens, where the MFMAs start to show (16 tokens: even to +2%, 18% with 64 of
+// 128 experts active; 12.5 tokens: +2% evenly spread, -2% same-domain), or 32
+// where the reduction is short and an item's start weighs more (256 values:
+// 9 and 16 tokens -6% and -7%, 62 tokens +14%).  MXFP4 streams a quarter of
+// the bytes and gains from the start (T = 65: +2%, 256: +3%, and +17% where 32
+// experts are active).
+template <int MODE, int FMT>
+bool ffn_wide_pays(int T, int K, int E, int rows, int kdim) {
+  const long long items = (long long)wide_tiles<MODE>(rows) * (E + T * K / kWideTokens);
+  return T > 64 && items >= 300 && (FMT == kMxfp4 || T * K >= (kdim >= 512 ? 16 : 32) * E);
+}
+
+// Launches the wide kernel (and sets a.tiles).
+template <int MODE, int FMT>
+void launch_ffn_wide(FfnArgs a, int T, int K, int E, hipStream_t s);
+
+}  // namespace eldr
