@@ -53,6 +53,7 @@
 #include <mutex>
 
 #include "ffn_common.hpp"
+#include "ffn_slim.hpp"
 #include "ffn_wide.hpp"
 
 namespace eldr {
@@ -958,6 +959,10 @@ static void launch_ffn(FfnArgs a, int T, int K, int E, hipStream_t s) {
 // whole-expert dealing, each workgroup building the buckets itself.
 template <int FMT>
 static void launch_ffn_routed(const FfnArgs& a, int T, int E, hipStream_t s) {
+  if (ffn_slim_pays<kUp, FMT>(T, a.K, E, a.rows, a.kdim)) {
+    launch_ffn_slim<kUp, FMT, true>(a, T, a.K, E, s);
+    return;
+  }
   const int per_xcd = (E + kNumXcd - 1) / kNumXcd;
   const dim3 grid(kNumXcd * a.tiles * per_xcd), block(ffn_threads<kUp, FMT>());
   if (T <= 16)
@@ -985,6 +990,10 @@ static void launch_ffn_fused(const FfnArgs& up, const FfnArgs& dn, int32_t* sync
 
 template <int MODE, int FMT>
 static void launch_ffn_nt(const FfnArgs& a, int T, int K, int E, hipStream_t s) {
+  if (ffn_slim_pays<MODE, FMT>(T, K, E, a.rows, a.kdim)) {
+    launch_ffn_slim<MODE, FMT, false>(a, T, K, E, s);
+    return;
+  }
   if (ffn_wide_pays<MODE, FMT>(T, K, E, a.rows, a.kdim)) {
     launch_ffn_wide<MODE, FMT>(a, T, K, E, s);
     return;
