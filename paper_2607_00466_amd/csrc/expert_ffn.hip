@@ -792,18 +792,32 @@ void ffn_kernel(FfnArgs a) {
       ffn_item<MODE, NT, FMT, kEarly, false, false, false>(a, L, e, slot % a.tiles, s_begin, 0,
                                                     min(c, kGroupTokens), NoHook{}, NoHook{});
   } else {
-    deal_large_batch<kGroupTokens, false>(
-        a, xcd, slot, slots,
-        [&](const int e, const int tile, const int s_begin, const int p0, const int c, const bool whole,
-            const bool shared) __attribute__((always_inline)) {
-          if (whole)
-            ffn_item<MODE, NT, FMT, MODE == kDown, false, false, false>(a, L, e, tile, s_begin, p0, c, NoHook{},
-                                                                       NoHook{});
-          else if (shared)
-            ffn_item<MODE, NT, FMT, kEarly, false, true, false>(a, L, e, tile, s_begin, p0, c, NoHook{}, NoHook{});
-          else
-            ffn_item<MODE, NT, FMT, kEarly, false, false, false>(a, L, e, tile, s_begin, p0, c, NoHook{}, NoHook{});
-        });
+    const UnionLanes L4 = load_union(a);
+    if (union_max(L4) <= kGroupTokens) {
+      // When every bucket fits one token group, the batch is not skewed enough
+      // to need the band dealing: whole experts go round-robin over the XCDs as
+      // for small batches, so that an expert's activations (x rows for up, h
+      // for down) are fetched into one XCD's L2 rather than into all eight.
+      const int u = (slot / a.tiles) * kNumXcd + xcd;
+      if (u >= L4.U || u >= a.experts) return;  // also covers U < 0 (invalid routing)
+      const UnionEntry x = union_entry(L4, u);
+      if (x.c > 0)
+        ffn_item<MODE, NT, FMT, MODE == kDown, false, false, false>(a, L, x.e, slot % a.tiles, x.sb, 0, x.c, NoHook{},
+                                                                   NoHook{});
+      return;
+    }
+    __shared__ ItemTable tab;
+    auto groups = [](const int c) { return (c + kGroupTokens - 1) / kGroupTokens; };
+    const int total = deal_bands(a, L4, tab, xcd, groups);
+    for (int it = slot; it < total; it += slots) {
+      const Item x = find_item(a, tab, xcd, it, groups);
+      const int p0 = x.group * kGroupTokens;
+      const int c = min(kGroupTokens, x.c - p0);
+      if (x.groups > 1)
+        ffn_item<MODE, NT, FMT, kEarly, false, true, false>(a, L, x.e, x.tile, x.sb, p0, c, NoHook{}, NoHook{});
+      else
+        ffn_item<MODE, NT, FMT, kEarly, false, false, false>(a, L, x.e, x.tile, x.sb, p0, c, NoHook{}, NoHook{});
+    }
   }
 }
 

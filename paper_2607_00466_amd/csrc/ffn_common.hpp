@@ -119,135 +119,146 @@ __device__ __forceinline__ int wave_inclusive_sum(int x) {
 }
 
 
-// Work items of a batch whose buckets may exceed one token group of GROUP
-// tokens: calls item(e, band, first slot of the bucket, first token of the
-// group, tokens, whole, shared) for each; whole: whole experts are dealt (one
-// item a workgroup), shared: the band is read by other groups too.
-//
-// The union lists its experts in dispatch order (moe_bucket: more
-// 16-token tiles first).  A projection's units are (expert, row band)
-// pairs in that order, band by band: unit tiles * u + t is band t of the
-// expert at union position u, and unit k goes to XCD k % 8.  So every XCD gets an
-// equal share of every expert's bands (exactly equal when the band count
-// is a multiple of 8, within one band otherwise) and the XCDs' loads match
-// however skewed the buckets are; an XCD's items follow the union order,
-// so the largest buckets start first; and an expert's items there are its
-// bands in order with each band's token groups adjacent, reading the same
-// weights side by side through the XCD's L2.
-//
-// Every wave holds the whole union, four positions a lane (4 * lane + j;
-// union_ids is -1 past the union and is read together with union_size):
-// id, bucket start and size, and the first item and number of items of
-// the expert on this XCD.  Loads are issued unconditionally (from clamped
-// indices), so the wave waits for two round trips rather than one a slot.
-template <int GROUP, bool EVEN, class Item>
-__device__ __forceinline__ void deal_large_batch(const FfnArgs& a, const int xcd, const int slot, const int slots,
-                                                 Item&& item) {
-  const int lane = threadIdx.x % kWave;
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+// The union of a large batch, held by every wave: positions 4 lane + j in
+// dispatch order (union_ids is -1 past the union and is read together with
+// union_size): id, bucket start and size (0 past the union, or for an invalid
+// routing).  Loads are issued unconditionally (from clamped indices), so the
+// wave waits for two round trips rather than one a position.
+struct UnionLanes {
+  int e[4], sb[4], c[4];
+  int U;
+};
+
+__device__ __forceinline__ UnionLanes load_union(const FfnArgs& a) {
   static_assert(MOE_MAX_E <= 4 * kWave, "four union positions a lane");
-  int e_j[4], sb_j[4], hi_j[4], c_j[4], n_j[4], first_j[4];
+  const int lane = threadIdx.x % kWave;
+  UnionLanes L;
+  int hi[4];
 #pragma unroll
-  for (int j = 0; j < 4; ++j) e_j[j] = a.union_ids[min(4 * lane + j, a.experts - 1)];
-  const int U = *a.union_size;  // U <= 0 (empty or invalid routing): no items
+  for (int j = 0; j < 4; ++j) L.e[j] = a.union_ids[min(4 * lane + j, a.experts - 1)];
+  L.U = *a.union_size;  // U <= 0 (empty or invalid routing): no items
 #pragma unroll
   for (int j = 0; j < 4; ++j) {
-    const int ec = e_j[j] >= 0 && e_j[j] < a.experts ? e_j[j] : 0;
-    sb_j[j] = a.offsets[ec];
-    hi_j[j] = a.offsets[ec + 1];
+    const int ec = L.e[j] >= 0 && L.e[j] < a.experts ? L.e[j] : 0;
+    L.sb[j] = a.offsets[ec];
+    hi[j] = a.offsets[ec + 1];
   }
   // (keeps the compiler from sinking a load into the branch that uses it)
 #pragma unroll
-  for (int j = 0; j < 4; ++j) asm volatile("" : "+v"(sb_j[j]), "+v"(hi_j[j]));
-  int lane_n = 0;
+  for (int j = 0; j < 4; ++j) asm volatile("" : "+v"(L.sb[j]), "+v"(hi[j]));
 #pragma unroll
   for (int j = 0; j < 4; ++j) {
-    const int u = 4 * lane + j;
-    const bool member = u < min(U, a.experts) && e_j[j] >= 0 && e_j[j] < a.experts;
-    c_j[j] = member ? max(hi_j[j] - sb_j[j], 0) : 0;
-    const int g = (c_j[j] + GROUP - 1) / GROUP;
-    const int band0 = (xcd - a.tiles * u) & (kNumXcd - 1);  // first band on this XCD
+    const bool member = 4 * lane + j < min(L.U, a.experts) && L.e[j] >= 0 && L.e[j] < a.experts;
+    L.c[j] = member ? max(hi[j] - L.sb[j], 0) : 0;
+  }
+  return L;
+}
+
+// The largest bucket (uniform).
+__device__ __forceinline__ int union_max(const UnionLanes& L) {
+  int m = max(max(L.c[0], L.c[1]), max(L.c[2], L.c[3]));
+#pragma unroll
+  for (int off = kWave / 2; off > 0; off >>= 1) m = max(m, __shfl_xor(m, off));
+  return __builtin_amdgcn_readfirstlane(m);
+}
+
+// Union position u's entries, from the lane that holds them (u uniform).
+struct UnionEntry {
+  int e, sb, c;
+};
+__device__ __forceinline__ UnionEntry union_entry(const UnionLanes& L, const int u) {
+  UnionEntry r{0, 0, 0};
+  const int ls = u / 4, js = u % 4;
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    if (j == js) {
+      r.e = __builtin_amdgcn_readlane(L.e[j], ls);
+      r.sb = __builtin_amdgcn_readlane(L.sb[j], ls);
+      r.c = __builtin_amdgcn_readlane(L.c[j], ls);
+    }
+  }
+  return r;
+}
+
+// The items of one XCD when (expert, row band) units are dealt round-robin.
+// The union lists its experts in dispatch order (moe_bucket: more 16-token
+// tiles first); unit tiles * u + t is band t of the expert at union position
+// u, and unit k goes to XCD k % 8.  So every XCD gets an equal share of every
+// expert's bands (exactly equal when the band count is a multiple of 8, within
+// one band otherwise) and the XCDs' loads match however skewed the buckets
+// are; an XCD's items follow the union order, so the largest buckets start
+// first; and an expert's items there are its bands in order with each band's
+// token groups adjacent, reading the same weights side by side through the
+// XCD's L2.  The table lies in LDS for the item loop: held in registers it
+// would stay live across every item and crowd the 128-token passes.
+struct ItemTable {
+  int4 first[kWave], n[kWave], c[kWave], e[kWave], sb[kWave];
+};
+struct Item {
+  int e, tile, sb, c, group, groups;  // c: tokens of the whole bucket
+};
+
+// Fills the table (uniform; ends with a barrier) and returns the item count.
+template <class Groups>
+__device__ __forceinline__ int deal_bands(const FfnArgs& a, const UnionLanes& L, ItemTable& tab, const int xcd,
+                                          Groups&& groups) {
+  const int lane = threadIdx.x % kWave;
+  int n[4], first[4], lane_n = 0;
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    const int band0 = (xcd - a.tiles * (4 * lane + j)) & (kNumXcd - 1);  // first band on this XCD
     const int nb = band0 < a.tiles ? (a.tiles - 1 - band0) / kNumXcd + 1 : 0;
-    n_j[j] = nb * g;
-    first_j[j] = lane_n;
-    lane_n += n_j[j];
+    n[j] = nb * groups(L.c[j]);
+    first[j] = lane_n;
+    lane_n += n[j];
   }
-  // When every bucket fits one token group, the batch is not skewed enough
-  // to need the band dealing: whole experts go round-robin over the XCDs as
-  // for small batches, so that an expert's activations (x rows for up, h
-  // for down) are fetched into one XCD's L2 rather than into all eight.
-  int cmax = max(max(c_j[0], c_j[1]), max(c_j[2], c_j[3]));
-#pragma unroll
-  for (int off = kWave / 2; off > 0; off >>= 1) cmax = max(cmax, __shfl_xor(cmax, off));
-  const bool whole = __builtin_amdgcn_readfirstlane(cmax) <= GROUP;
-  int total = slot + 1, w_e = 0, w_sb = 0, w_c = 0;
-  // The table moves to LDS for the item loop: held in registers it would
-  // stay live across every item and crowd the 128-token passes.
-  __shared__ int4 lk_first[kWave], lk_n[kWave], lk_c[kWave], lk_e[kWave], lk_sb[kWave];
-  if (whole) {
-    const int u = (slot / a.tiles) * kNumXcd + xcd;
-    if (u >= U || u >= a.experts) return;  // also covers U < 0 (invalid routing)
-    // union position u: its entries, from the lane that holds them
-    const int ls = u / 4, js = u % 4;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      if (j == js) {
-        w_e = __builtin_amdgcn_readlane(e_j[j], ls);
-        w_sb = __builtin_amdgcn_readlane(sb_j[j], ls);
-        w_c = __builtin_amdgcn_readlane(c_j[j], ls);
-      }
-    }
-  } else {
-    const int incl = wave_inclusive_sum(lane_n);
-    total = __builtin_amdgcn_readlane(incl, kWave - 1);
-    if (slot >= total) return;
-    if (wave == 0) {
-      const int f0 = incl - lane_n;
-      lk_first[lane] = make_int4(first_j[0] + f0, first_j[1] + f0, first_j[2] + f0, first_j[3] + f0);
-      lk_n[lane] = make_int4(n_j[0], n_j[1], n_j[2], n_j[3]);
-      lk_c[lane] = make_int4(c_j[0], c_j[1], c_j[2], c_j[3]);
-      lk_e[lane] = make_int4(e_j[0], e_j[1], e_j[2], e_j[3]);
-      lk_sb[lane] = make_int4(sb_j[0], sb_j[1], sb_j[2], sb_j[3]);
-    }
-    __syncthreads();
+  const int incl = wave_inclusive_sum(lane_n);
+  const int total = __builtin_amdgcn_readlane(incl, kWave - 1);
+  if (threadIdx.x < kWave) {
+    const int f0 = incl - lane_n;
+    tab.first[lane] = make_int4(first[0] + f0, first[1] + f0, first[2] + f0, first[3] + f0);
+    tab.n[lane] = make_int4(n[0], n[1], n[2], n[3]);
+    tab.c[lane] = make_int4(L.c[0], L.c[1], L.c[2], L.c[3]);
+    tab.e[lane] = make_int4(L.e[0], L.e[1], L.e[2], L.e[3]);
+    tab.sb[lane] = make_int4(L.sb[0], L.sb[1], L.sb[2], L.sb[3]);
   }
-  for (int it = slot; it < total; it += slots) {
-    if (whole) {
-      if (w_c > 0) item(w_e, slot % a.tiles, w_sb, 0, w_c, true, false);
-      break;
-    }
-    // the union position whose items cover this one
-    const int4 f4 = lk_first[lane];
-    const int4 n4 = lk_n[lane];
-    const int fj[4] = {f4.x, f4.y, f4.z, f4.w};
-    const int nj[4] = {n4.x, n4.y, n4.z, n4.w};
-    int js = -1, ls = 0;
+  __syncthreads();
+  return total;
+}
+
+// Item `it` of the XCD (it < deal_bands' count): the union position whose
+// items cover it, its band and its token group.
+template <class Groups>
+__device__ __forceinline__ Item find_item(const FfnArgs& a, const ItemTable& tab, const int xcd, const int it,
+                                          Groups&& groups) {
+  const int lane = threadIdx.x % kWave;
+  const int4 f4 = tab.first[lane];
+  const int4 n4 = tab.n[lane];
+  const int fj[4] = {f4.x, f4.y, f4.z, f4.w};
+  const int nj[4] = {n4.x, n4.y, n4.z, n4.w};
+  int js = 0, ls = 0;
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const unsigned long long hit = __ballot(nj[j] > 0 && fj[j] <= it && it < fj[j] + nj[j]);
-      if (hit != 0) {
-        js = j;
-        ls = __ffsll(hit) - 1;
-      }
+  for (int j = 0; j < 4; ++j) {
+    const unsigned long long hit = __ballot(nj[j] > 0 && fj[j] <= it && it < fj[j] + nj[j]);
+    if (hit != 0) {
+      js = j;
+      ls = __ffsll(hit) - 1;
     }
-    if (js < 0) break;  // not reached: the ranges cover [0, total)
-    js = __builtin_amdgcn_readfirstlane(js);
-    ls = __builtin_amdgcn_readfirstlane(ls);
-    // union position 4 * ls + js: its entries, read at a uniform address
-    auto pick = [&](const int4* v) { return reinterpret_cast<const int*>(v)[4 * ls + js]; };
-    const int cu = pick(lk_c);
-    const int g = (cu + GROUP - 1) / GROUP;
-    const int r = it - pick(lk_first);
-    const int band = r / g;
-    const int group = r - band * g;
-    const int tile = ((xcd - a.tiles * (4 * ls + js)) & (kNumXcd - 1)) + kNumXcd * band;
-    // An expert's groups: GROUP tokens each and the rest in the last, or (EVEN)
-    // as many whole tiles in each as make them equal within one tile.
-    const int per = EVEN ? ((cu + 15) / 16 + g - 1) / g * 16 : GROUP;
-    const int p0 = group * per;
-    const int c = min(per, cu - p0);
-    if (c > 0) item(pick(lk_e), tile, pick(lk_sb), p0, c, false, g > 1);
   }
+  js = __builtin_amdgcn_readfirstlane(js);
+  ls = __builtin_amdgcn_readfirstlane(ls);
+  // union position 4 * ls + js: its entries, read at a uniform address
+  auto pick = [&](const int4* v) { return reinterpret_cast<const int*>(v)[4 * ls + js]; };
+  Item r;
+  r.c = pick(tab.c);
+  r.groups = groups(r.c);
+  const int k = it - pick(tab.first);
+  const int band = k / r.groups;
+  r.group = k - band * r.groups;
+  r.tile = ((xcd - a.tiles * (4 * ls + js)) & (kNumXcd - 1)) + kNumXcd * band;
+  r.e = pick(tab.e);
+  r.sb = pick(tab.sb);
+  return r;
 }
 
 }  // namespace eldr

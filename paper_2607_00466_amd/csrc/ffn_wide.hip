@@ -35,6 +35,12 @@
 namespace eldr {
 
 constexpr int kWideThreads = 256;  // 4 waves
+// Items below which token groups are cut smaller: one for each CU.  The host
+// sees the batch, not the union: where locality leaves few experts, 128-token
+// items would leave CUs idle (MXFP4, gpt-oss shape, T = 278 in 5 experts:
+// 183 -> 142 us; 300 tokens in 12 Qwen3 experts: 101 -> 97), while a bound of
+// 512 cut groups that did not need it (T = 300 in 32 experts: 108 -> 127).
+constexpr int kWideFill = 256;
 constexpr int kWideBuf = 32768;    // bytes of one staging buffer: 16 fragment pairs of 2 KB
 
 // One item: expert e's wave slots from 8 tile on by the c tokens (1 .. 16 NTB)
@@ -276,26 +282,67 @@ template <int MODE, int FMT>
 __global__ __launch_bounds__(kWideThreads) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void ffn_wide_kernel(FfnArgs a) {
   __shared__ __attribute__((aligned(16))) unsigned char lds[2][kWideBuf];
-  deal_large_batch<kWideTokens, true>(
-      a, blockIdx.x % kNumXcd, blockIdx.x / kNumXcd, gridDim.x / kNumXcd,
-      [&](int e, int tile, int s_begin, int p0, int c, bool, bool shared) __attribute__((always_inline)) {
-        e = __builtin_amdgcn_readfirstlane(e);
-        tile = __builtin_amdgcn_readfirstlane(tile);
-        const int first = __builtin_amdgcn_readfirstlane(s_begin + p0);
-        c = __builtin_amdgcn_readfirstlane(c);
-        if (c > 64) {
-          if (shared)
-            wide_pass<MODE, FMT, 8, true>(a, lds, e, tile, first, c);
-          else
-            wide_pass<MODE, FMT, 8, false>(a, lds, e, tile, first, c);
-        } else if (c > 32) {
-          wide_pass<MODE, FMT, 4, false>(a, lds, e, tile, first, c);
-        } else if (c > 16) {
-          wide_pass<MODE, FMT, 2, false>(a, lds, e, tile, first, c);
-        } else {
-          wide_pass<MODE, FMT, 1, false>(a, lds, e, tile, first, c);
-        }
-      });
+  __shared__ ItemTable tab;
+  const int xcd = blockIdx.x % kNumXcd;
+  const int slot = blockIdx.x / kNumXcd;
+  const int slots = gridDim.x / kNumXcd;
+  UnionLanes L = load_union(a);
+  // Tokens an item takes at most: 128, or 64 or 32 where the union's buckets
+  // would make fewer than kWideFill items of that size.
+  int cap = kWideTokens;
+  for (; cap > 32; cap /= 2) {
+    int n = 0;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) n += (L.c[j] + cap - 1) / cap;
+    if (a.tiles * __builtin_amdgcn_readlane(wave_inclusive_sum(n), kWave - 1) >= kWideFill) break;
+  }
+  // Whole experts are dealt while every bucket is one item's, else bands.
+  const bool whole = union_max(L) <= cap;
+  auto groups = [cap](const int c) { return (c + cap - 1) / cap; };
+  UnionEntry x{0, 0, 0};
+  int total = slot + 1;
+  if (whole) {
+    const int u = (slot / a.tiles) * kNumXcd + xcd;
+    if (u >= L.U || u >= a.experts) return;  // also covers U < 0 (invalid routing)
+    x = union_entry(L, u);
+    if (x.c <= 0) return;
+  } else {
+    total = deal_bands(a, L, tab, xcd, groups);
+  }
+  for (int it = slot; it < total; it += slots) {
+    int e = x.e, tile = slot % a.tiles, first = x.sb, c = x.c;
+    bool shared = false;
+    if (!whole) {
+      const Item m = find_item(a, tab, xcd, it, groups);
+      // groups of as many whole tiles as make them equal within one
+      const int per = ((m.c + 15) / 16 + m.groups - 1) / m.groups * 16;
+      e = m.e;
+      tile = m.tile;
+      first = m.sb + m.group * per;
+      c = min(per, m.c - m.group * per);
+      shared = m.groups > 1;
+    }
+    e = __builtin_amdgcn_readfirstlane(e);
+    tile = __builtin_amdgcn_readfirstlane(tile);
+    first = __builtin_amdgcn_readfirstlane(first);
+    c = __builtin_amdgcn_readfirstlane(c);
+    auto pass = [&](auto NTB) __attribute__((always_inline)) {
+      constexpr int n = decltype(NTB)::value;
+      if (shared)
+        wide_pass<MODE, FMT, n, true>(a, lds, e, tile, first, c);
+      else
+        wide_pass<MODE, FMT, n, false>(a, lds, e, tile, first, c);
+    };
+    if (c > 64)
+      pass(Int<8>{});
+    else if (c > 32)
+      pass(Int<4>{});
+    else if (c > 16)
+      pass(Int<2>{});
+    else
+      pass(Int<1>{});
+    if (whole) break;
+  }
 }
 
 template <int MODE, int FMT>

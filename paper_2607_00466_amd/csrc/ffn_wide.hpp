@@ -23,12 +23,13 @@ constexpr int wide_tiles(int rows) {
 // 128 experts active; 12.5 tokens: +2% evenly spread, -2% same-domain), or 32
 // where the reduction is short and an item's start weighs more (256 values:
 // 9 and 16 tokens -6% and -7%, 62 tokens +14%).  MXFP4 streams a quarter of
-// the bytes and gains from the start (T = 65: +2%, 256: +3%, and +17% where 32
-// experts are active).
+// the bytes and gains earlier, from 4 tokens (gpt-oss shape: T = 128 +5%, 256
+// +3%, and +7% and +22% where 32 experts are active; at T = 80, 2.5 tokens,
+// with 4 experts active -5%).
 template <int MODE, int FMT>
 bool ffn_wide_pays(int T, int K, int E, int rows, int kdim) {
   const long long items = (long long)wide_tiles<MODE>(rows) * (E + T * K / kWideTokens);
-  return T > 64 && items >= 300 && (FMT == kMxfp4 || T * K >= (kdim >= 512 ? 16 : 32) * E);
+  return T > 64 && items >= 300 && T * K >= (FMT == kMxfp4 ? 4 : kdim >= 512 ? 16 : 32) * E;
 }
 
 // Launches the wide kernel (and sets a.tiles).

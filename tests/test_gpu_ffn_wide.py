@@ -62,3 +62,19 @@ def test_bucket_sizes_around_every_tile(fmt, H, I):
     for n in (40, 64):
         part = _run(layer, n, ids, w)
         assert np.array_equal(g["out"][:n], part["out"]), f"first {n} tokens differ"
+
+
+@pytest.mark.parametrize("fmt,H,I", [("bf16", 352, 288), ("bf16", 288, 32), ("mxfp4", 320, 192)])
+def test_few_active_experts_take_smaller_groups(fmt, H, I):
+    # 4 experts hold every token: 17 groups of 128 tokens each make 204 items of
+    # 3 row bands (cut to 64 tokens), or 68 of one (cut to 32), for 256 CUs.
+    E, K, T = 248, 4, 2080
+    G.say(f"case: {fmt} E={E} top-{K} H={H} I={I} T={T}, 4 experts active")
+    sh = synth.LayerShape(f"few_{fmt}", E=E, K=K, H=H, I=I)
+    layer = G.Layer(sh, T, seed=I) if fmt == "bf16" else MX.MxLayer(sh, T, seed=I)
+    ids, w, _ = synth.controlled_routing(T, E, K, U=4, seed=I)
+    g = _run(layer, T, ids, w)
+    if fmt == "bf16":
+        P._full_check(layer, g, False, routing=(ids.astype(np.int64), w))
+    else:
+        MX._check_layer(layer, g, (ids, w))
