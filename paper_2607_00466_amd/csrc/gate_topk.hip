@@ -16,16 +16,40 @@ namespace eldr {
 constexpr int kGateWaves = ELDR_GATE_WAVES;  // the reduction axis H is split over the waves
 constexpr int kGateThreads = kGateWaves * 64;
 
+// The value of lane ^ M (M a power of two below 16), within rows of 16 lanes.
+template <int M>
+__device__ __forceinline__ float lane_xor(float v) {
+  static_assert(M == 1 || M == 2 || M == 4 || M == 8, "within a row");
+  const int x = __float_as_int(v);
+  if constexpr (M == 1) return __int_as_float(__builtin_amdgcn_update_dpp(x, x, 0xb1, 0xf, 0xf, false));  // quad_perm 1,0,3,2
+  if constexpr (M == 2) return __int_as_float(__builtin_amdgcn_update_dpp(x, x, 0x4e, 0xf, 0xf, false));  // quad_perm 2,3,0,1
+  if constexpr (M == 4) {  // ^ 7 (row_half_mirror), then ^ 3 (quad_perm 3,2,1,0)
+    const int h = __builtin_amdgcn_update_dpp(x, x, 0x141, 0xf, 0xf, false);
+    return __int_as_float(__builtin_amdgcn_update_dpp(h, h, 0x1b, 0xf, 0xf, false));
+  }
+  return __int_as_float(__builtin_amdgcn_update_dpp(x, x, 0x128, 0xf, 0xf, false));  // row_ror:8
+}
+
 // One step of the halving butterfly over the first 2 * HALF entries of acc:
 // a lane keeps the half selected by lane bit M and adds its partner's copy.
+// Across rows of 16 lanes a lane swap does selection and exchange at once: of
+// a pair (a, b) the lower lanes end with a and the partner's a, the upper
+// ones with b and the partner's b.
 template <int HALF, int M>
 __device__ __forceinline__ void halving_step(float* acc, int lane) {
   const bool upper = (lane & M) != 0;
 #pragma unroll
   for (int i = 0; i < HALF; ++i) {
-    const float mine = upper ? acc[i + HALF] : acc[i];
-    const float other = upper ? acc[i] : acc[i + HALF];
-    acc[i] = mine + __shfl_xor(other, M);
+    if constexpr (M >= 16) {
+      const uint32_t a = __float_as_uint(acc[i]), b = __float_as_uint(acc[i + HALF]);
+      const auto r = M == 32 ? __builtin_amdgcn_permlane32_swap(a, b, false, false)
+                             : __builtin_amdgcn_permlane16_swap(a, b, false, false);
+      acc[i] = __uint_as_float(r[0]) + __uint_as_float(r[1]);
+    } else {
+      const float mine = upper ? acc[i + HALF] : acc[i];
+      const float other = upper ? acc[i] : acc[i + HALF];
+      acc[i] = mine + lane_xor<M>(other);
+    }
   }
 }
 
@@ -39,7 +63,7 @@ __device__ __forceinline__ void lane_reduce(float* acc, int lane) {
   if constexpr (COUNT >= 2) {
     halving_step<COUNT / 2, M>(acc, lane);
   } else {
-    acc[0] += __shfl_xor(acc[0], M);
+    acc[0] += lane_xor<M>(acc[0]);
   }
   if constexpr (M > 1) lane_reduce<(COUNT >= 2 ? COUNT / 2 : 1), M / 2>(acc, lane);
 }
@@ -52,7 +76,14 @@ __device__ __forceinline__ void lane_reduce(float* acc, int lane) {
 // of a score depends on H alone: experts with identical gate rows get
 // bitwise-identical scores, and a token's scores do not depend on the tile
 // shape or on the other tokens of the batch.
-template <int TT, int TE>
+//
+// VALU and latency bound it: 4 fused multiply-adds a lane, pair and position,
+// which at H = 2048 come to two positions a lane, then the reduction.  That was
+// 63 exchanges through LDS a 8 x 8 tile, each with two selections; lane swaps
+// (across rows) and DPP (within them) leave an add and a swap.  Scores and
+// selection, before -> after: T = 1000 (H 2048, E 128) 25.3 -> 21.4 us,
+// T = 2048 (H 2880) 55.9 -> 47.3, T = 256 10.7 -> 10.0, T = 1 6.5 -> 6.0.
+template <int TT, int TE, bool BY_TOKEN>
 __global__ __launch_bounds__(kGateThreads) void gate_scores_kernel(const float* __restrict__ x,
                                                           const float* __restrict__ wg, int T,
                                                           int H, int E,
@@ -62,46 +93,49 @@ __global__ __launch_bounds__(kGateThreads) void gate_scores_kernel(const float* 
   __shared__ float part[kGateWaves][kOut];
   const int wave = threadIdx.x / kWave;
   const int lane = threadIdx.x % kWave;
-  const int e0 = blockIdx.x * TE;
-  const int t0 = blockIdx.y * TT;
+  int e0, t0;
+  if constexpr (BY_TOKEN) {
+    // XCD b % 8 takes token tiles b % 8, + 8, ..., each against every expert tile
+    const int tiles_e = (E + TE - 1) / TE;
+    const int slot = blockIdx.x / kNumXcd;
+    t0 = (slot / tiles_e * kNumXcd + (int)(blockIdx.x % kNumXcd)) * TT;
+    e0 = slot % tiles_e * TE;
+    if (t0 >= T) return;
+  } else {
+    e0 = blockIdx.x * TE;
+    t0 = blockIdx.y * TT;
+  }
   const int H4 = H / 4;
   const int q_begin = (H4 * wave) / kGateWaves;
   const int q_end = (H4 * (wave + 1)) / kGateWaves;
 
   const float4* wrow[TE];
-  bool wok[TE];
 #pragma unroll
-  for (int a = 0; a < TE; ++a) {
-    wok[a] = (e0 + a) < E;
-    wrow[a] = reinterpret_cast<const float4*>(wg + (size_t)(wok[a] ? e0 + a : 0) * H);
-  }
+  for (int a = 0; a < TE; ++a) wrow[a] = reinterpret_cast<const float4*>(wg + (size_t)(e0 + a < E ? e0 + a : 0) * H);
   const float4* xrow[TT];
-  bool xok[TT];
 #pragma unroll
-  for (int j = 0; j < TT; ++j) {
-    xok[j] = (t0 + j) < T;
-    xrow[j] = reinterpret_cast<const float4*>(x + (size_t)(xok[j] ? t0 + j : 0) * H);
-  }
+  for (int j = 0; j < TT; ++j) xrow[j] = reinterpret_cast<const float4*>(x + (size_t)(t0 + j < T ? t0 + j : 0) * H);
 
   float acc[kOut];
 #pragma unroll
   for (int i = 0; i < kOut; ++i) acc[i] = 0.0f;
 
+  // (rows past E or T re-read row 0; their sums are not stored)
   for (int q = q_begin + lane; q < q_end; q += kWave) {
-    float4 w[TE];
+    float4 w[TE], xv[TT];
 #pragma unroll
-    for (int a = 0; a < TE; ++a)
-      w[a] = wok[a] ? wrow[a][q] : make_float4(0.f, 0.f, 0.f, 0.f);
+    for (int a = 0; a < TE; ++a) w[a] = wrow[a][q];
+#pragma unroll
+    for (int j = 0; j < TT; ++j) xv[j] = xrow[j][q];
 #pragma unroll
     for (int j = 0; j < TT; ++j) {
-      const float4 xv = xok[j] ? xrow[j][q] : make_float4(0.f, 0.f, 0.f, 0.f);
 #pragma unroll
       for (int a = 0; a < TE; ++a) {
         float s = acc[a * TT + j];
-        s = fmaf(w[a].x, xv.x, s);
-        s = fmaf(w[a].y, xv.y, s);
-        s = fmaf(w[a].z, xv.z, s);
-        s = fmaf(w[a].w, xv.w, s);
+        s = fmaf(w[a].x, xv[j].x, s);
+        s = fmaf(w[a].y, xv[j].y, s);
+        s = fmaf(w[a].z, xv[j].z, s);
+        s = fmaf(w[a].w, xv[j].w, s);
         acc[a * TT + j] = s;
       }
     }
@@ -211,17 +245,23 @@ extern "C" int moe_gate_topk(const float* x, const float* w_gate, moe_dims d, fl
   hipStream_t s = reinterpret_cast<hipStream_t>(stream);
   // Tiles of 4 tokens x 4 experts up to 128 tokens: the most workgroups for a
   // reduction that is one or two loads a lane long.  Above that 8 x 8: half
-  // the L2 reads of x and of the gate rows per product (measured on MI355X at
-  // H = 2880: 11.1 -> 8.2 us at T = 256 against 8 x 4 tiles on 8 waves, and
-  // 3.9 us at T = 64 against 4.1).  The scores are the same bits either way.
+  // the loads of x and of the gate rows per product (16 x 8 and 8 x 16 measured
+  // even from T = 512 and 15% slower at 256; 16 x 16 30% slower).  The scores
+  // are the same bits either way.  Above 256 tokens x outweighs the gate rows,
+  // so an XCD takes whole token tiles and reads its share of x once, where a
+  // grid with the experts innermost has every XCD read all of it (T = 1000:
+  // 23.5 -> 22.2 us, T = 200: 9.5 -> 9.7).
+  const dim3 block(eldr::kGateThreads);
   if (d.T <= 128) {
-    dim3 g1((d.E + 3) / 4, (d.T + 3) / 4);
-    hipLaunchKernelGGL((eldr::gate_scores_kernel<4, 4>), g1, dim3(eldr::kGateThreads), 0, s, x, w_gate,
-                       d.T, d.H, d.E, logits);
+    const dim3 g1((d.E + 3) / 4, (d.T + 3) / 4);
+    hipLaunchKernelGGL((eldr::gate_scores_kernel<4, 4, false>), g1, block, 0, s, x, w_gate, d.T, d.H, d.E, logits);
+  } else if (d.T <= 256) {
+    const dim3 g1((d.E + 7) / 8, (d.T + 7) / 8);
+    hipLaunchKernelGGL((eldr::gate_scores_kernel<8, 8, false>), g1, block, 0, s, x, w_gate, d.T, d.H, d.E, logits);
   } else {
-    dim3 g1((d.E + 7) / 8, (d.T + 7) / 8);
-    hipLaunchKernelGGL((eldr::gate_scores_kernel<8, 8>), g1, dim3(eldr::kGateThreads), 0, s, x, w_gate,
-                       d.T, d.H, d.E, logits);
+    const int per_xcd = ((d.T + 7) / 8 + eldr::kNumXcd - 1) / eldr::kNumXcd;  // token tiles
+    const dim3 g1(eldr::kNumXcd * per_xcd * ((d.E + 7) / 8));
+    hipLaunchKernelGGL((eldr::gate_scores_kernel<8, 8, true>), g1, block, 0, s, x, w_gate, d.T, d.H, d.E, logits);
   }
   st = launch_status();
   if (st != MOE_OK) return st;
