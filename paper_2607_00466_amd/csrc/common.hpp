@@ -17,24 +17,6 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 // keep in registers when it is copied whole).
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
-// fp32 -> bf16 bit pattern, round to nearest even (inputs are finite; a NaN
-// keeps a quiet-NaN pattern).
-__device__ __forceinline__ uint32_t f32_to_bf16_bits(float f) {
-  uint32_t u = __float_as_uint(f);
-  if ((u & 0x7fffffffu) > 0x7f800000u) return (u >> 16) | 0x40u;
-  u += 0x7fffu + ((u >> 16) & 1u);
-  return u >> 16;
-}
-
-__device__ __forceinline__ float bf16_bits_to_f32(uint32_t b) { return __uint_as_float(b << 16); }
-
-// Split v into hi + lo, both bf16: hi = rne(v), lo = rne(v - hi).  v - hi is
-// exact in fp32, so hi + lo carries about 16 significant bits of v.
-__device__ __forceinline__ void split_bf16(float v, uint32_t& hi, uint32_t& lo) {
-  hi = f32_to_bf16_bits(v);
-  lo = f32_to_bf16_bits(v - bf16_bits_to_f32(hi));
-}
-
 __device__ __forceinline__ bf16x8 as_bf16x8(u32x4 v) { return __builtin_bit_cast(bf16x8, v); }
 
 // 16x16x32 bf16 MFMA with fp32 accumulation.  A lane supplies 8 k-values of

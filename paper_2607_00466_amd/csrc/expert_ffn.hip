@@ -535,22 +535,22 @@ __device__ __forceinline__ void ffn_item(const FfnArgs& a, FfnLds<FMT, NT>& L, c
             if (ok0) {
               // h for rows r0 + rsub .. + 3: half of one 8-value group of the
               // split layout (high parts at +0, low parts at +16 bytes).
-              uint32_t hi[4], lo[4];
+              uint32_t v[4], hi[2], lo[2];
   #pragma unroll
-              for (int i = 0; i < 4; ++i) split_bf16(silu(acc0[t][i]) * acc1[t][i], hi[i], lo[i]);
+              for (int i = 0; i < 4; ++i) v[i] = __float_as_uint(silu(acc0[t][i]) * acc1[t][i]);
+              split2(v[0], v[1], hi[0], lo[0]);
+              split2(v[2], v[3], hi[1], lo[1]);
               const int col = r0 + rsub;
               unsigned char* row = static_cast<unsigned char*>(a.dst) + sl * (size_t)a.rows * 4;
               unsigned char* grp = row + (col / 8) * 32 + (col % 8) * 2;
               if constexpr (WT) {
-                const uint64_t h64 = (uint64_t)(hi[0] | (hi[1] << 16)) | ((uint64_t)(hi[2] | (hi[3] << 16)) << 32);
-                const uint64_t l64 = (uint64_t)(lo[0] | (lo[1] << 16)) | ((uint64_t)(lo[2] | (lo[3] << 16)) << 32);
-                __hip_atomic_store(reinterpret_cast<uint64_t*>(grp), h64, __ATOMIC_RELAXED,
-                                   __HIP_MEMORY_SCOPE_AGENT);
-                __hip_atomic_store(reinterpret_cast<uint64_t*>(grp + 16), l64, __ATOMIC_RELAXED,
-                                   __HIP_MEMORY_SCOPE_AGENT);
+                __hip_atomic_store(reinterpret_cast<uint64_t*>(grp), (uint64_t)hi[0] | ((uint64_t)hi[1] << 32),
+                                   __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                __hip_atomic_store(reinterpret_cast<uint64_t*>(grp + 16), (uint64_t)lo[0] | ((uint64_t)lo[1] << 32),
+                                   __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
               } else {
-                *reinterpret_cast<uint2*>(grp) = make_uint2(hi[0] | (hi[1] << 16), hi[2] | (hi[3] << 16));
-                *reinterpret_cast<uint2*>(grp + 16) = make_uint2(lo[0] | (lo[1] << 16), lo[2] | (lo[3] << 16));
+                *reinterpret_cast<uint2*>(grp) = make_uint2(hi[0], hi[1]);
+                *reinterpret_cast<uint2*>(grp + 16) = make_uint2(lo[0], lo[1]);
               }
             }
           } else {
