@@ -20,29 +20,22 @@
 // by ascending id -- so the FFN starts its longest items first while batches
 // of small buckets stream the experts in address order.  An expert's
 // dispatch position is the number of experts with a larger (tiles, -id) key.
-#include <algorithm>
-
 #include "common.hpp"
+#include "dispatch.hpp"
 
 namespace eldr {
 
 constexpr int kBucketThreads = 1024;
-constexpr int kBucketMaxWords = 16384;  // E * ceil(T / 32) limit (64 KiB of bitmaps)
 constexpr int kOrderTokens = 16;        // union order: buckets compared in tiles of 16 tokens
-constexpr int kBucketSmall = 256;       // tokens of a batch counted by one thread an expert
-constexpr int kBucketPairs = 2048;      // pairs a workgroup writes: two a thread
-constexpr int kBucketMaxWgs = 16;
 
-// Words from one expert's bitmap to the next: odd, so that the lanes of a
-// wave, which set bits of a few words of many experts, hit different LDS banks.
-__host__ __device__ constexpr int bucket_stride(int T) { return ((T + 31) / 32) | 1; }
-
-// LARGE: batches of more than kBucketSmall tokens.
-template <bool LARGE>
+// LARGE: batches of more than kBucketSmall tokens.  IN_PLACE: pair_pos holds
+// the ids and is overwritten.
+template <bool LARGE, bool IN_PLACE>
 __global__ __launch_bounds__(kBucketThreads) void bucket_kernel(
-    const int32_t* __restrict__ ids, int T, int E, int K, int32_t* __restrict__ counts,
+    const int32_t* __restrict__ topk_ids, int T, int E, int K, int32_t* __restrict__ counts,
     int32_t* __restrict__ offsets, int32_t* __restrict__ perm_token, int32_t* __restrict__ pair_pos,
     int32_t* __restrict__ union_ids, int32_t* __restrict__ union_size) {
+  const int32_t* ids = IN_PLACE ? pair_pos : topk_ids;
   extern __shared__ uint32_t smem[];
   // union order keys, larger first: 16-token tiles (<= 256) above 255 - e
   // (e < 256); 0 past E, below every expert with tokens
@@ -230,11 +223,6 @@ __global__ __launch_bounds__(kBucketThreads) void bucket_kernel(
   }
 }
 
-size_t bucket_lds_bytes(int T, int E) {
-  const size_t EW = (size_t)E * bucket_stride(T);
-  return EW * 4 + ((EW + 1) & ~(size_t)1) * 2 + (size_t)E * 4 * 4;
-}
-
 }  // namespace eldr
 
 extern "C" int moe_bucket(const int32_t* topk_ids, moe_dims d, int32_t* counts, int32_t* offsets,
@@ -249,27 +237,18 @@ extern "C" int moe_bucket(const int32_t* topk_ids, moe_dims d, int32_t* counts, 
       !aligned4(pair_pos) || !aligned4(union_ids) || !aligned4(union_size))
     return MOE_ERR_UNSUPPORTED;
   if ((long long)d.E * ((d.T + 31) / 32) > eldr::kBucketMaxWords) return MOE_ERR_UNSUPPORTED;
-  const size_t lds = eldr::bucket_lds_bytes(d.T, d.E);
-  const bool large = d.T > eldr::kBucketSmall;
+  const bool in_place = topk_ids == pair_pos;
+  const eldr::BucketLaunch l = eldr::bucket_launch(d.T, d.E, d.K, in_place);
+  const auto kernel = l.large ? (in_place ? eldr::bucket_kernel<true, true> : eldr::bucket_kernel<true, false>)
+                              : (in_place ? eldr::bucket_kernel<false, true> : eldr::bucket_kernel<false, false>);
   // Bitmaps above 64 KiB (about 8192 words) need the kernel's dynamic LDS
   // limit raised, on the current device, before the launch; the call is cheap
   // and shapes that need it are prefill-sized, so it is made on every such
   // call rather than cached.
-  if (lds > 64 * 1024 &&
-      hipFuncSetAttribute(reinterpret_cast<const void*>(eldr::bucket_kernel<true>),
-                          hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess)
+  if (l.lds > 64 * 1024 && hipFuncSetAttribute(reinterpret_cast<const void*>(kernel),
+                                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)l.lds) != hipSuccess)
     return MOE_ERR_HIP;
-  hipStream_t s = reinterpret_cast<hipStream_t>(stream);
-  // One workgroup up to 2048 pairs (a decode batch of 256 tokens at top-8),
-  // then as many as leave each about that many to write, up to 16: past that
-  // every workgroup's own pass over the ids is most of its time.
-  const int wgs = std::min(eldr::kBucketMaxWgs, (d.T * d.K + eldr::kBucketPairs - 1) / eldr::kBucketPairs);
-  const dim3 grid(std::max(1, wgs)), block(eldr::kBucketThreads);
-  if (large)
-    hipLaunchKernelGGL(eldr::bucket_kernel<true>, grid, block, lds, s, topk_ids, d.T, d.E, d.K, counts, offsets,
-                       perm_token, pair_pos, union_ids, union_size);
-  else
-    hipLaunchKernelGGL(eldr::bucket_kernel<false>, grid, block, lds, s, topk_ids, d.T, d.E, d.K, counts, offsets,
-                       perm_token, pair_pos, union_ids, union_size);
+  hipLaunchKernelGGL(kernel, dim3(l.wgs), dim3(eldr::kBucketThreads), l.lds, reinterpret_cast<hipStream_t>(stream),
+                     topk_ids, d.T, d.E, d.K, counts, offsets, perm_token, pair_pos, union_ids, union_size);
   return launch_status();
 }

@@ -1,0 +1,27 @@
+// Asks the launch rules of csrc/dispatch.hpp: one query a line of standard
+// input, one line of numbers each on standard output.
+#include <cstdio>
+#include <cstdlib>
+#include <iostream>
+#include <sstream>
+#include <string>
+
+#include "dispatch.hpp"
+
+int main() {
+  std::string line;
+  while (std::getline(std::cin, line)) {
+    std::istringstream in(line);
+    std::string what;
+    in >> what;
+    if (what == "bucket") {  // T E K, pair_pos over topk_ids
+      int T, E, K, in_place;
+      in >> T >> E >> K >> in_place;
+      const auto l = eldr::bucket_launch(T, E, K, in_place);
+      std::printf("%d %d %zu\n", l.large, l.wgs, l.lds);
+    } else {
+      return 2;
+    }
+    if (!in) return 3;
+  }
+}

@@ -1,0 +1,39 @@
+"""The host's launch rules (csrc/dispatch.hpp), asked by a small program: no GPU."""
+import os
+import shutil
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+CSRC = os.path.join(ROOT, "paper_2607_00466_amd", "csrc")
+
+pytestmark = pytest.mark.skipif(shutil.which("g++") is None, reason="needs g++")
+
+
+@pytest.fixture(scope="module")
+def ask(tmp_path_factory):
+    """ask(queries) -> one list of numbers a query."""
+    exe = str(tmp_path_factory.mktemp("rules") / "dispatch_rules")
+    r = subprocess.run(["g++", "-O1", "-std=c++17", "-Wall", "-Werror", "-I", os.path.join(ROOT, "include"), "-I", CSRC,
+                        os.path.join(ROOT, "tests", "dispatch_rules.cpp"), "-o", exe],
+                       capture_output=True, text=True, timeout=300)
+    assert r.returncode == 0, r.stderr[-2000:]
+
+    def run(queries):
+        queries = [" ".join(map(str, q)) for q in queries]
+        out = subprocess.run([exe], input="\n".join(queries) + "\n", capture_output=True, text=True, timeout=60)
+        assert out.returncode == 0, out.stderr
+        lines = out.stdout.splitlines()
+        assert len(lines) == len(queries)
+        return [[int(v) for v in l.split()] for l in lines]
+
+    return run
+
+
+def test_bucket_in_place_is_one_workgroup(ask):
+    # several workgroups would read all the ids while each replaces a stretch of them
+    for T, E, K, wgs in [(0, 37, 16, 1), (128, 37, 16, 1), (129, 37, 16, 2), (1024, 128, 8, 4), (4096, 128, 8, 16)]:
+        (large, apart, lds), over = ask([("bucket", T, E, K, 0), ("bucket", T, E, K, 1)])
+        assert apart == wgs
+        assert over == [large, 1, lds]

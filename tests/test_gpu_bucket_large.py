@@ -12,13 +12,16 @@ from tests import gpu_util as G
 pytestmark = pytest.mark.gpu
 
 
-def _bucket(ids, E):
+def _bucket(ids, E, in_place=False):
     T, K = ids.shape
     d = B.dims(T, 64, E, K, 32)
     buf = B.LayerBuffers.allocate(d)
     for t in (buf.counts, buf.offsets, buf.perm_token, buf.pair_pos, buf.union_ids, buf.union_size):
         t.fill_(-7)
-    B.moe_bucket(torch.from_numpy(np.ascontiguousarray(ids, np.int32)).cuda(), d, buf.counts, buf.offsets,
+    dev = torch.from_numpy(np.ascontiguousarray(ids, np.int32)).cuda()
+    if in_place:
+        buf.pair_pos = dev.view(-1)
+    B.moe_bucket(dev, d, buf.counts, buf.offsets,
                  buf.perm_token, buf.pair_pos, buf.union_ids, buf.union_size)
     torch.cuda.synchronize()
     return G.fetch(buf, d)
@@ -33,6 +36,14 @@ def test_bucket_launch_rules(T, E, K):
     few = min(E, K + 2)
     ids = np.stack([rng.choice(few if t % 2 else E, K, replace=False) for t in range(T)]).astype(np.int32)
     G.compare_buckets(_bucket(ids, E), ids.astype(np.int64), E)
+
+
+@pytest.mark.parametrize("T,E,K", [(64, 16, 4), (256, 9, 8), (300, 40, 8), (4096, 37, 16)])
+def test_bucket_in_place(T, E, K):
+    # pair_pos written over topk_ids, in batches of one workgroup's pairs and of more
+    G.say(f"case: bucket only, in place, T={T} E={E} K={K}")
+    ids = np.stack([np.random.default_rng(t).choice(E, K, replace=False) for t in range(T)]).astype(np.int32)
+    G.compare_buckets(_bucket(ids, E, in_place=True), ids.astype(np.int64), E)
 
 
 @pytest.mark.parametrize("where", [0, 1, -1])
