@@ -148,11 +148,17 @@ def _ptr(t: torch.Tensor | None):
     return None if t is None else t.data_ptr()
 
 
+# The current stream's address without a Stream object (a private name of torch's).
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream(stream) -> int:
-    """The hipStream_t of a torch stream (None: the current one) or of its address."""
-    if stream is None:
-        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
-    return stream if type(stream) is int else stream.cuda_stream
+    """The hipStream_t of a torch stream (None: the current one)."""
+    if stream is not None:
+        return stream.cuda_stream
+    if _raw_stream is None:
+        return torch.cuda.current_stream().cuda_stream
+    return _raw_stream(torch.cuda.current_device())
 
 
 def _need(t: torch.Tensor, name: str, dtype: torch.dtype, numel: int) -> None:
