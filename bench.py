@@ -23,9 +23,11 @@ JSON lines; ``--point T:U`` times single controlled points only).
 from __future__ import annotations
 
 import argparse
+import hashlib
 import json
 import math
 import os
+import re
 import sys
 import time
 
@@ -50,19 +52,38 @@ PROFILE = os.path.join(ROOT, "profiles", "moe_layer_qwen3_30b_a3b_T64.md")
 FFN_SOURCE = os.path.join(ROOT, "paper_2607_00466_amd", "csrc", "expert_ffn.hip")
 
 
+def ffn_sources(source: str = FFN_SOURCE) -> list[str]:
+    """The FFN's source and every file beside it that it includes, at any
+    depth: the kernel, what it calls, and the rules that choose it."""
+    found, todo = [], [source]
+    while todo:
+        path = todo.pop()
+        if path in found or not os.path.exists(path):
+            continue
+        found.append(path)
+        names = re.findall(r'^#include "([^"]+)"', open(path).read(), re.M)
+        todo += [os.path.join(os.path.dirname(path), n) for n in names]
+    return sorted(found)
+
+
+def ffn_source_key(source: str = FFN_SOURCE) -> str:
+    """The key by which a profile names the code it was taken from."""
+    h = hashlib.sha256()
+    for path in ffn_sources(source):
+        h.update(os.path.basename(path).encode() + b"\0" + open(path, "rb").read() + b"\0")
+    return h.hexdigest()[:16]
+
+
 def measured_traffic() -> int | None:
     """HBM bytes per FFN-up launch from the committed rocprofv3 counter profile
     (FETCH_SIZE + WRITE_SIZE, calibrated against a 1 GiB copy), or None when the
-    kernel source has changed since the counters were taken."""
-    import hashlib
-
+    FFN's sources have changed since the counters were taken."""
     try:
         text = open(PROFILE).read()
     except OSError:
         return None
     fields = dict(l.split(": ", 1) for l in text.splitlines() if ": " in l and not l.startswith(("|", "#", "`")))
-    src = hashlib.sha256(open(FFN_SOURCE, "rb").read()).hexdigest()[:16]
-    if fields.get("expert_ffn_source_sha256_16", "").strip() != src:
+    if fields.get("ffn_sources_sha256_16", "").strip() != ffn_source_key():
         return None
     try:
         return int(float(fields["traffic_bytes_per_launch (ffn up, read + write)"]))
