@@ -45,4 +45,27 @@ inline BucketLaunch bucket_launch(int T, int E, int K, bool in_place) {
   return {T > kBucketSmall, in_place ? 1 : std::max(1, wgs), bucket_lds_bytes(T, E)};
 }
 
+// --------------------------------------------------------------- gate scores
+
+struct GateLaunch {
+  int tile;       // tokens and experts of a workgroup's tile
+  bool by_token;  // an XCD takes whole token tiles, each against every expert tile
+};
+
+// Tiles of 4 tokens x 4 experts up to 128 tokens: the most workgroups for a
+// reduction that is one or two loads a lane long.  Above that 8 x 8: half the
+// loads of x and of the gate rows per product (16 x 8 and 8 x 16 measured even
+// from T = 512 and 15% slower at 256; 16 x 16 30% slower).  The scores are the
+// same bits either way.  Above 256 tokens x outweighs the gate rows, so an XCD
+// takes whole token tiles and reads its share of x once, where a grid with the
+// experts innermost has every XCD read all of it (E = 128, H = 2048: T = 1000
+// 23.5 -> 22.2 us, T = 200 9.5 -> 9.7).  But then every XCD reads all the gate
+// rows for each of its token tiles, which pays while they fit its 4 MB of L2:
+// E = 256, H = 4096 (4 MiB) T = 2048 110.9 -> 105.0 us, H = 7168 (7 MiB) 173.2
+// -> 250.1.
+constexpr long long kGateRowBytes = 4ll << 20;
+inline GateLaunch gate_launch(int T, int E, int H) {
+  return {T <= 128 ? 4 : 8, T > 256 && 4ll * E * H <= kGateRowBytes};
+}
+
 }  // namespace eldr

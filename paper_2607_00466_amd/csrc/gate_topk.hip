@@ -7,6 +7,7 @@
 #include <math.h>
 
 #include "common.hpp"
+#include "dispatch.hpp"
 
 namespace eldr {
 
@@ -243,25 +244,17 @@ extern "C" int moe_gate_topk(const float* x, const float* w_gate, moe_dims d, fl
       !aligned4(topk_w))
     return MOE_ERR_UNSUPPORTED;
   hipStream_t s = reinterpret_cast<hipStream_t>(stream);
-  // Tiles of 4 tokens x 4 experts up to 128 tokens: the most workgroups for a
-  // reduction that is one or two loads a lane long.  Above that 8 x 8: half
-  // the loads of x and of the gate rows per product (16 x 8 and 8 x 16 measured
-  // even from T = 512 and 15% slower at 256; 16 x 16 30% slower).  The scores
-  // are the same bits either way.  Above 256 tokens x outweighs the gate rows,
-  // so an XCD takes whole token tiles and reads its share of x once, where a
-  // grid with the experts innermost has every XCD read all of it (T = 1000:
-  // 23.5 -> 22.2 us, T = 200: 9.5 -> 9.7).
   const dim3 block(eldr::kGateThreads);
-  if (d.T <= 128) {
-    const dim3 g1((d.E + 3) / 4, (d.T + 3) / 4);
-    hipLaunchKernelGGL((eldr::gate_scores_kernel<4, 4, false>), g1, block, 0, s, x, w_gate, d.T, d.H, d.E, logits);
-  } else if (d.T <= 256) {
-    const dim3 g1((d.E + 7) / 8, (d.T + 7) / 8);
+  const eldr::GateLaunch l = eldr::gate_launch(d.T, d.E, d.H);
+  const dim3 g1((d.E + l.tile - 1) / l.tile, (d.T + l.tile - 1) / l.tile);
+  if (l.by_token) {
+    const int per_xcd = (g1.y + eldr::kNumXcd - 1) / eldr::kNumXcd;  // token tiles
+    hipLaunchKernelGGL((eldr::gate_scores_kernel<8, 8, true>), dim3(eldr::kNumXcd * per_xcd * g1.x), block, 0, s, x,
+                       w_gate, d.T, d.H, d.E, logits);
+  } else if (l.tile == 8) {
     hipLaunchKernelGGL((eldr::gate_scores_kernel<8, 8, false>), g1, block, 0, s, x, w_gate, d.T, d.H, d.E, logits);
   } else {
-    const int per_xcd = ((d.T + 7) / 8 + eldr::kNumXcd - 1) / eldr::kNumXcd;  // token tiles
-    const dim3 g1(eldr::kNumXcd * per_xcd * ((d.E + 7) / 8));
-    hipLaunchKernelGGL((eldr::gate_scores_kernel<8, 8, true>), g1, block, 0, s, x, w_gate, d.T, d.H, d.E, logits);
+    hipLaunchKernelGGL((eldr::gate_scores_kernel<4, 4, false>), g1, block, 0, s, x, w_gate, d.T, d.H, d.E, logits);
   }
   st = launch_status();
   if (st != MOE_OK) return st;

@@ -19,6 +19,11 @@ int main() {
       in >> T >> E >> K >> in_place;
       const auto l = eldr::bucket_launch(T, E, K, in_place);
       std::printf("%d %d %zu\n", l.large, l.wgs, l.lds);
+    } else if (what == "gate") {  // T E H
+      int T, E, H;
+      in >> T >> E >> H;
+      const auto l = eldr::gate_launch(T, E, H);
+      std::printf("%d %d\n", l.tile, l.by_token);
     } else {
       return 2;
     }

@@ -37,3 +37,11 @@ def test_bucket_in_place_is_one_workgroup(ask):
         (large, apart, lds), over = ask([("bucket", T, E, K, 0), ("bucket", T, E, K, 1)])
         assert apart == wgs
         assert over == [large, 1, lds]
+
+
+def test_gate_tokens_go_by_xcd_while_the_gate_rows_fit_its_cache(ask):
+    for T, E, H, tile, by_token in [(128, 128, 2048, 4, 0), (129, 128, 2048, 8, 0), (256, 128, 2048, 8, 0),
+                                    (257, 128, 2048, 8, 1), (4096, 1, 32, 8, 1), (4096, 128, 2880, 8, 1),
+                                    (257, 256, 4096, 8, 1), (257, 256, 4128, 8, 0), (4096, 256, 7168, 8, 0),
+                                    (4096, 256, 16384, 8, 0), (4096, 64, 16384, 8, 1), (4096, 65, 16384, 8, 0)]:
+        assert ask([("gate", T, E, H)]) == [[tile, by_token]], (T, E, H)

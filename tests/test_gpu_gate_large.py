@@ -1,7 +1,7 @@
 """Gate scores of batches on both sides of the tile switches (128 and 256
-tokens), with partial expert and token tiles, reductions of less than one
-position a lane and of several, and a last XCD round with few token tiles:
-against the oracle, and the same bits as in batches of 4 x 4 tiles."""
+tokens; gate rows of more than 4 MiB), with partial expert and token tiles,
+reductions of less than one position a lane and of several, and a last XCD
+round with few token tiles: against the oracle, and the same bits as in batches of 4 x 4 tiles."""
 import numpy as np
 import pytest
 import torch
@@ -14,7 +14,8 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("T,E,K,H", [(129, 13, 4, 1056), (256, 9, 2, 32), (257, 13, 4, 2880), (263, 256, 16, 96),
-                                     (321, 1, 1, 4160), (1025, 60, 3, 544)])
+                                     (321, 1, 1, 4160), (1025, 60, 3, 544),
+                                     (258, 256, 8, 4128), (265, 129, 5, 8192)])
 def test_gate_tiles_and_reductions(T, E, K, H):
     G.say(f"case: gate only, T={T} E={E} top-{K} H={H}")
     sh = synth.LayerShape("gate", E=E, K=K, H=H, I=32)
