@@ -28,7 +28,7 @@ namespace eldr {
 constexpr int kBucketThreads = 1024;
 constexpr int kOrderTokens = 16;        // union order: buckets compared in tiles of 16 tokens
 
-// LARGE: batches of more than kBucketSmall tokens.  IN_PLACE: pair_pos holds
+// LARGE: several threads an expert (see bucket_launch).  IN_PLACE: pair_pos holds
 // the ids and is overwritten.
 template <bool LARGE, bool IN_PLACE>
 __global__ __launch_bounds__(kBucketThreads) void bucket_kernel(

@@ -14,7 +14,8 @@ namespace eldr {
 // ----------------------------------------------------------------- moe_bucket
 
 constexpr int kBucketMaxWords = 16384;  // E * ceil(T / 32) limit
-constexpr int kBucketSmall = 256;       // tokens of a batch counted by one thread an expert
+constexpr int kBucketSmall = 256;       // tokens, and
+constexpr int kBucketFew = 3072;        // pairs, of a batch counted by one thread an expert
 constexpr int kBucketPairs = 2048;      // pairs a workgroup writes: two a thread
 constexpr int kBucketMaxWgs = 16;
 
@@ -34,6 +35,12 @@ struct BucketLaunch {
   size_t lds;
 };
 
+// Several threads an expert, with eight ids in flight each, pay once a thread
+// has more than about three pairs and an expert more than 8 words (one thread an
+// expert against several: T = 300 top-8 of 128, 2400 pairs, 4.74 us against 5.47;
+// T = 512 top-4 of 128 4.91 against 5.74; T = 700 top-2 of 8 4.17 against 4.75;
+// but T = 512 top-8, 4096 pairs, 7.3 against 6.0).
+//
 // One workgroup up to 2048 pairs (a decode batch of 256 tokens at top-8), then
 // as many as leave each about that many to write, up to 16: past that every
 // workgroup's own pass over the ids is most of its time.  With pair_pos written
@@ -42,7 +49,7 @@ struct BucketLaunch {
 // might still be counting.
 inline BucketLaunch bucket_launch(int T, int E, int K, bool in_place) {
   const int wgs = std::min(kBucketMaxWgs, (T * K + kBucketPairs - 1) / kBucketPairs);
-  return {T > kBucketSmall, in_place ? 1 : std::max(1, wgs), bucket_lds_bytes(T, E)};
+  return {T > kBucketSmall && T * K > kBucketFew, in_place ? 1 : std::max(1, wgs), bucket_lds_bytes(T, E)};
 }
 
 // --------------------------------------------------------------- gate scores

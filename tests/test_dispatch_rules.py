@@ -39,6 +39,14 @@ def test_bucket_in_place_is_one_workgroup(ask):
         assert over == [large, 1, lds]
 
 
+def test_bucket_threads_an_expert(ask):
+    # (few pairs in many tokens are counted faster by one thread an expert)
+    for T, E, K, large in [(256, 16, 16, 0), (257, 128, 8, 0), (300, 128, 8, 0), (384, 128, 8, 0), (385, 128, 8, 1),
+                           (700, 8, 2, 0), (1536, 8, 2, 0), (1537, 8, 2, 1), (768, 128, 4, 0), (769, 128, 4, 1),
+                           (3072, 170, 1, 0), (4096, 128, 1, 1)]:
+        assert ask([("bucket", T, E, K, 0)])[0][0] == large, (T, E, K)
+
+
 def test_gate_tokens_go_by_xcd_while_the_gate_rows_fit_its_cache(ask):
     for T, E, H, tile, by_token in [(128, 128, 2048, 4, 0), (129, 128, 2048, 8, 0), (256, 128, 2048, 8, 0),
                                     (257, 128, 2048, 8, 1), (4096, 1, 32, 8, 1), (4096, 128, 2880, 8, 1),

@@ -1,6 +1,7 @@
 """moe_bucket at the edges of its launch rules: one or several workgroups
-(2048 pairs each, up to 16), one or several threads an expert (256 tokens; 64
-and 128 experts), a partial last bitmap word, and invalid routing that another
+(2048 pairs each, up to 16), one or several threads an expert (256 tokens and
+3072 pairs; 64 and 128 experts), bitmaps above and below 64 KiB of either, a
+partial last bitmap word, and invalid routing that another
 workgroup's stretch of the pairs holds."""
 import numpy as np
 import pytest
@@ -28,7 +29,8 @@ def _bucket(ids, E, in_place=False):
 
 
 @pytest.mark.parametrize("T,E,K", [(256, 9, 8), (257, 9, 8), (257, 16, 1), (2049, 64, 1), (1000, 65, 5),
-                                   (1025, 129, 16), (4095, 128, 8), (4096, 37, 16), (300, 1, 1)])
+                                   (1025, 129, 16), (4095, 128, 8), (4096, 37, 16), (300, 1, 1),
+                                   (384, 128, 8), (385, 128, 8), (768, 256, 4), (3072, 170, 1), (3073, 168, 1)])
 def test_bucket_launch_rules(T, E, K):
     G.say(f"case: bucket only, T={T} E={E} K={K}")
     rng = np.random.default_rng(T + E + K)
