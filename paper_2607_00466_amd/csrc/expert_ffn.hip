@@ -813,6 +813,11 @@ void ffn_kernel(FfnArgs a) {
       const Item x = find_item(a, tab, xcd, it, groups);
       const int p0 = x.group * kGroupTokens;
       const int c = min(kGroupTokens, x.c - p0);
+      // Not reached (no group is empty), but the compiler then knows c > 0:
+      // without it the 128-token kernels took 2 to 8% longer on buckets of
+      // several groups (256 tokens in 2 experts of H 4096, I 14336, down: 293.7
+      // us with it, 312.6 without; in 4 of the gpt-oss shape, up: 104.7, 107.9).
+      if (c <= 0) continue;
       if (x.groups > 1)
         ffn_item<MODE, NT, FMT, kEarly, false, true, false>(a, L, x.e, x.tile, x.sb, p0, c, NoHook{}, NoHook{});
       else
