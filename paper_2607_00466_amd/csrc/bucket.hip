@@ -21,7 +21,6 @@
 // of small buckets stream the experts in address order.  An expert's
 // dispatch position is the number of experts with a larger (tiles, -id) key.
 #include "common.hpp"
-#include "dispatch.hpp"
 
 namespace eldr {
 

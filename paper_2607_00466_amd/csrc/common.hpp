@@ -4,12 +4,12 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "dispatch.hpp"
 #include "eldr_moe.h"
 
 namespace eldr {
 
 constexpr int kWave = 64;    // CDNA wavefront width
-constexpr int kNumXcd = 8;   // MI355X: 8 XCDs, workgroups dispatched round-robin over them
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));

@@ -11,6 +11,8 @@
 
 namespace eldr {
 
+constexpr int kNumXcd = 8;  // MI355X: 8 XCDs, workgroups dispatched round-robin over them
+
 // ----------------------------------------------------------------- moe_bucket
 
 constexpr int kBucketMaxWords = 16384;  // E * ceil(T / 32) limit
@@ -73,6 +75,56 @@ struct GateLaunch {
 constexpr long long kGateRowBytes = 4ll << 20;
 inline GateLaunch gate_launch(int T, int E, int H) {
   return {T <= 128 ? 4 : 8, T > 256 && 4ll * E * H <= kGateRowBytes};
+}
+
+// ----------------------------------------------------------------- expert FFN
+
+// Weight formats.
+//   kBf16:  packed by moe_pack_up_weights / moe_pack_down_weights; a ring
+//           slot is one k-step of the wave's two 16-row tiles, two adjacent
+//           1 KB loads.
+//   kMxfp4: packed by moe_pack_mxfp4_up / _down; a ring slot is two k-steps
+//           of the wave's two 16-row tiles: one 1 KB load of FP4 codes (a
+//           lane's 16 bytes are its 8 codes of tile 0 step 0, tile 0 step 1,
+//           tile 1 step 0, tile 1 step 1) and one 64-byte load of their E8M0
+//           scales (a dword per row, its bytes in the same order).  For up the
+//           two tiles are W1's and W3's rows of the band, for down two
+//           adjacent 16-row tiles of W2.
+enum WeightFmt { kBf16 = 0, kMxfp4 = 1 };
+
+enum FfnMode { kUp = 0, kDown = 1 };
+
+constexpr int kSlimTokens = 4;
+
+// Whether the one-wave kernel runs a projection (`rows` output rows an expert,
+// reductions of `kdim`) of a batch of T tokens.  Up to 4 tokens the union is
+// small (at most T K experts) and the four-wave items of the other kernel leave
+// CUs idle or unevenly loaded; measured up + down, with every shape tried ahead:
+// T = 1 +12 to +44%, T = 4 +2 to +28%.  From 8 tokens its waves each staging the
+// activations for themselves costs more than it gains where buckets fill (T = 8
+// in 4 experts, MXFP4: -16%; bf16 T = 8: -3%).  The other kernel keeps
+// * an up projection with so many one-wave items that an XCD's 32 CUs run them in
+//   several rounds: bf16, 768 an XCD (64 experts, H = 2048, I = 3072) -4%, 896 (8
+//   experts, H = 4096, I = 14336) -6 to -11%, while 360 and 384 (gpt-oss shape; 32
+//   experts, H = 4096, I = 3072) give -10 to +1% where T K experts are active and
+//   +9 to +13% where the tokens share theirs, and 192 +2 to +44%; MXFP4 gains up
+//   to 768 (+2 to +23%) and at 896 with 1 and 2 tokens (+11 to +23%), with 3 and
+//   4 it loses 4 to 8% of the layer;
+// * from 3 tokens, a down projection over so many values that every wave stages
+//   the activations again and again (14336: the layer -4 to -8%);
+// * a bf16 down projection with several four-wave items for each of the 256 CUs,
+//   or with one where the reduction is too short to make up for a start of its
+//   own in every wave (768 values, T = 2 and 4: -7% and -9%; 1024, T = 2 to 4:
+//   -3%; 1408, T = 4 in 16 experts: -13%; 3072, T = 4 in 27 experts: -10%).
+inline bool ffn_slim_pays(FfnMode mode, WeightFmt fmt, int T, int K, int E, int rows, int kdim) {
+  if (T > kSlimTokens) return false;
+  const int experts = std::min(E, T * K);
+  if (mode == kUp) {
+    const int xcd_items = rows / 16 * ((experts + kNumXcd - 1) / kNumXcd);
+    return fmt == kBf16 ? xcd_items <= 512 : T <= 2 || xcd_items <= 800;
+  }
+  if (T > 2 && kdim > 8192) return false;
+  return fmt == kMxfp4 || (rows + 127) / 128 * experts < (kdim < 1536 ? 256 : 512);
 }
 
 }  // namespace eldr

@@ -978,7 +978,7 @@ static void launch_ffn(FfnArgs a, int T, int K, int E, hipStream_t s) {
 // whole-expert dealing, each workgroup building the buckets itself.
 template <int FMT>
 static void launch_ffn_routed(const FfnArgs& a, int T, int E, hipStream_t s) {
-  if (ffn_slim_pays<kUp, FMT>(T, a.K, E, a.rows, a.kdim)) {
+  if (ffn_slim_pays(kUp, WeightFmt(FMT), T, a.K, E, a.rows, a.kdim)) {
     launch_ffn_slim<kUp, FMT, true>(a, T, a.K, E, s);
     return;
   }
@@ -1009,7 +1009,7 @@ static void launch_ffn_fused(const FfnArgs& up, const FfnArgs& dn, int32_t* sync
 
 template <int MODE, int FMT>
 static void launch_ffn_nt(const FfnArgs& a, int T, int K, int E, hipStream_t s) {
-  if (ffn_slim_pays<MODE, FMT>(T, K, E, a.rows, a.kdim)) {
+  if (ffn_slim_pays(FfnMode(MODE), WeightFmt(FMT), T, K, E, a.rows, a.kdim)) {
     launch_ffn_slim<MODE, FMT, false>(a, T, K, E, s);
     return;
   }

@@ -1,4 +1,4 @@
-// Shared by the expert FFN's kernels: weight formats, launch arguments, the
+// Shared by the expert FFN's kernels: launch arguments, the
 // bf16 pair split, the FP4 expansion and the dealing of a large batch's items.
 #pragma once
 
@@ -9,25 +9,10 @@ namespace eldr {
 constexpr int kKStep = 32;        // k per MFMA
 constexpr int kFragElems = 512;   // bf16 values in one packed 16 x 32 weight fragment (1 KB)
 
-// Weight formats.
-//   kBf16:  packed by moe_pack_up_weights / moe_pack_down_weights; a ring
-//           slot is one k-step of the wave's two 16-row tiles, two adjacent
-//           1 KB loads.
-//   kMxfp4: packed by moe_pack_mxfp4_up / _down; a ring slot is two k-steps
-//           of the wave's two 16-row tiles: one 1 KB load of FP4 codes (a
-//           lane's 16 bytes are its 8 codes of tile 0 step 0, tile 0 step 1,
-//           tile 1 step 0, tile 1 step 1) and one 64-byte load of their E8M0
-//           scales (a dword per row, its bytes in the same order).  For up the
-//           two tiles are W1's and W3's rows of the band, for down two
-//           adjacent 16-row tiles of W2.
-enum WeightFmt { kBf16 = 0, kMxfp4 = 1 };
-
 template <int FMT>
 __host__ __device__ constexpr int slot_steps() {
   return FMT == kBf16 ? 1 : 2;
 }
-
-enum FfnMode { kUp = 0, kDown = 1 };
 
 struct FfnArgs {
   const uint4* src;            // up: x [T, H] fp32; down: h [T*K, I] as bf16 pairs

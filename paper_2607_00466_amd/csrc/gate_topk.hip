@@ -7,7 +7,6 @@
 #include <math.h>
 
 #include "common.hpp"
-#include "dispatch.hpp"
 
 namespace eldr {
 

@@ -24,6 +24,10 @@ int main() {
       in >> T >> E >> H;
       const auto l = eldr::gate_launch(T, E, H);
       std::printf("%d %d\n", l.tile, l.by_token);
+    } else if (what == "slim") {  // mode format T K E rows kdim
+      int mode, fmt, T, K, E, rows, kdim;
+      in >> mode >> fmt >> T >> K >> E >> rows >> kdim;
+      std::printf("%d\n", eldr::ffn_slim_pays(eldr::FfnMode(mode), eldr::WeightFmt(fmt), T, K, E, rows, kdim));
     } else {
       return 2;
     }

@@ -8,6 +8,12 @@ import pytest
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 CSRC = os.path.join(ROOT, "paper_2607_00466_amd", "csrc")
 
+UP, DOWN = 0, 1
+BF16, MXFP4 = 0, 1
+QWEN = (8, 128, 2048, 768)       # K, E, H, I
+GPT_OSS = (4, 128, 2880, 2880)
+FEW_LARGE = (2, 8, 4096, 14336)  # a few large experts
+
 pytestmark = pytest.mark.skipif(shutil.which("g++") is None, reason="needs g++")
 
 
@@ -53,3 +59,45 @@ def test_gate_tokens_go_by_xcd_while_the_gate_rows_fit_its_cache(ask):
                                     (257, 256, 4096, 8, 1), (257, 256, 4128, 8, 0), (4096, 256, 7168, 8, 0),
                                     (4096, 256, 16384, 8, 0), (4096, 64, 16384, 8, 1), (4096, 65, 16384, 8, 0)]:
         assert ask([("gate", T, E, H)]) == [[tile, by_token]], (T, E, H)
+
+
+def _rows(mode, H, I):
+    """(output rows, reduction) of a projection."""
+    return (I, H) if mode == UP else (H, I)
+
+
+def _slim(ask, mode, fmt, T, shape):
+    K, E, H, I = shape
+    return ask([("slim", mode, fmt, T, K, E, *_rows(mode, H, I))])[0][0]
+
+
+@pytest.mark.parametrize("shape,fmt,up,down", [
+    (QWEN, BF16, (1, 1, 1, 1, 0), (1, 0, 0, 0, 0)),
+    (QWEN, MXFP4, (1, 1, 1, 1, 0), (1, 1, 1, 1, 0)),
+    (GPT_OSS, BF16, (1, 1, 1, 1, 0), (1, 1, 1, 1, 0)),
+    (GPT_OSS, MXFP4, (1, 1, 1, 1, 0), (1, 1, 1, 1, 0)),
+    ((4, 60, 2048, 1408), BF16, (1, 1, 1, 1, 0), (1, 1, 1, 0, 0)),
+    (FEW_LARGE, BF16, (0, 0, 0, 0, 0), (1, 1, 0, 0, 0)),
+    (FEW_LARGE, MXFP4, (1, 1, 0, 0, 0), (1, 1, 0, 0, 0)),
+    ((6, 64, 4096, 1024), BF16, (1, 1, 1, 1, 0), (1, 0, 0, 0, 0)),
+    ((8, 64, 2048, 3072), BF16, (1, 1, 0, 0, 0), (1, 1, 1, 0, 0)),
+    ((8, 64, 2048, 3072), MXFP4, (1, 1, 1, 1, 0), (1, 1, 1, 1, 0)),
+    ((1, 1, 32, 32), BF16, (1, 1, 1, 1, 0), (1, 1, 1, 1, 0)),
+])
+def test_one_wave_kernel(ask, shape, fmt, up, down):
+    # 1 .. 5 tokens
+    assert tuple(_slim(ask, UP, fmt, T, shape) for T in range(1, 6)) == up
+    assert tuple(_slim(ask, DOWN, fmt, T, shape) for T in range(1, 6)) == down
+
+
+def _cases(test):
+    """The parameter sets of a parametrised test."""
+    return next(m.args[1] for m in test.pytestmark if m.name == "parametrize")
+
+
+def test_the_one_wave_tests_run_that_kernel(ask):
+    from tests import test_gpu_ffn_slim as S
+    for fmt, H, I in _cases(S.test_bucket_sizes_and_reductions):
+        shape, f = (5, 40, H, I), BF16 if fmt == "bf16" else MXFP4
+        assert [_slim(ask, UP, f, T, shape) for T in (1, 2, 3, 4, 8)] == [1, 1, 1, 1, 0], (fmt, H, I)
+        assert [_slim(ask, DOWN, f, T, shape) for T in (1, 2, 3, 8)] == [1, 1, 1, 0], (fmt, H, I)
