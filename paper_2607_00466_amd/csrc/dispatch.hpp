@@ -127,4 +127,42 @@ inline bool ffn_slim_pays(FfnMode mode, WeightFmt fmt, int T, int K, int E, int 
   return fmt == kMxfp4 || (rows + 127) / 128 * experts < (kdim < 1536 ? 256 : 512);
 }
 
+constexpr int kWideTokens = 128;  // tokens of one item of the wide kernel
+
+// Items an expert's rows make for one token group: 128 rows of W1 and of W3
+// (up) or 256 rows of W2 (down) each.
+inline int wide_tiles(FfnMode mode, int rows) { return mode == kUp ? (rows + 127) / 128 : (rows + 255) / 256; }
+
+// Whether the wide kernel runs a projection of a batch of T > 64 tokens.  Its
+// items are twice as long as the small-batch kernel's, so there must be enough
+// of them to give every CU one: with E experts and T K / 128 further token
+// groups about 300 (measured: 312 items +4%, 330 items +15%, but 280 items
+// -6% and 171 items -14%).  With bf16 weights the buckets must also be large
+// enough for the MFMAs to show: 20 tokens on average for the up projection (25
+// tokens +6%; 16 tokens even, 18% with 64 of 128 experts active; 18.5 tokens
+// -1%; 12.5 tokens of one domain -2%) and 12 for the down projection, which
+// gains from staging h in whole lines (12.5 tokens +1%, of one domain +6%; 8
+// tokens -2%); 32 where the reduction is short and an item's start weighs more
+// (256 values: 9 and 16 tokens -6% and -7%, 62 tokens +14%).  MXFP4 streams a
+// quarter of the bytes and gains earlier, from 4 tokens (gpt-oss shape: T =
+// 128 +5%, 256 +3%, and +7% and +22% where 32 experts are active; at T = 80,
+// 2.5 tokens, with 4 experts active -5%).
+inline bool ffn_wide_pays(FfnMode mode, WeightFmt fmt, int T, int K, int E, int rows, int kdim) {
+  const long long items = (long long)wide_tiles(mode, rows) * (E + T * K / kWideTokens);
+  return T > 64 && items >= 300 && T * K >= (fmt == kMxfp4 ? 4 : kdim < 512 ? 32 : mode == kUp ? 20 : 12) * E;
+}
+
+// Workgroups of the wide kernel an XCD: an expert's bands for its share of E
+// experts and of the further groups of 128 tokens, but at least the two a CU
+// that are resident.  The device cuts groups smaller where few experts are
+// active, and with no more workgroups than 128-token groups would need, the
+// last few items made a second round (37 experts, H = 1056, I = 544, T = 1000:
+// 46 items an XCD on 40 workgroups, up 50.2 -> 38.2 us with 64).
+constexpr int kWideResident = 64;
+inline int wide_slots(int tiles, int T, int K, int E) {
+  const int per_xcd = (E + kNumXcd - 1) / kNumXcd;
+  const int extra = (T * K / kWideTokens + kNumXcd - 1) / kNumXcd;
+  return std::max(tiles * (per_xcd + extra), kWideResident);
+}
+
 }  // namespace eldr

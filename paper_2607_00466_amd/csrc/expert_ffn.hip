@@ -1013,7 +1013,7 @@ static void launch_ffn_nt(const FfnArgs& a, int T, int K, int E, hipStream_t s) 
     launch_ffn_slim<MODE, FMT, false>(a, T, K, E, s);
     return;
   }
-  if (ffn_wide_pays<MODE, FMT>(T, K, E, a.rows, a.kdim)) {
+  if (ffn_wide_pays(FfnMode(MODE), WeightFmt(FMT), T, K, E, a.rows, a.kdim)) {
     launch_ffn_wide<MODE, FMT>(a, T, K, E, s);
     return;
   }

@@ -347,10 +347,8 @@ void ffn_wide_kernel(FfnArgs a) {
 
 template <int MODE, int FMT>
 void launch_ffn_wide(FfnArgs a, int T, int K, int E, hipStream_t s) {
-  a.tiles = wide_tiles<MODE>(a.rows);
-  const int per_xcd = (E + kNumXcd - 1) / kNumXcd;
-  const int extra = (T * K / kWideTokens + kNumXcd - 1) / kNumXcd;
-  hipLaunchKernelGGL((ffn_wide_kernel<MODE, FMT>), dim3(kNumXcd * a.tiles * (per_xcd + extra)), dim3(kWideThreads), 0,
+  a.tiles = wide_tiles(FfnMode(MODE), a.rows);
+  hipLaunchKernelGGL((ffn_wide_kernel<MODE, FMT>), dim3(kNumXcd * wide_slots(a.tiles, T, K, E)), dim3(kWideThreads), 0,
                      s, a);
 }
 

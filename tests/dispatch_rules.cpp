@@ -28,6 +28,12 @@ int main() {
       int mode, fmt, T, K, E, rows, kdim;
       in >> mode >> fmt >> T >> K >> E >> rows >> kdim;
       std::printf("%d\n", eldr::ffn_slim_pays(eldr::FfnMode(mode), eldr::WeightFmt(fmt), T, K, E, rows, kdim));
+    } else if (what == "wide") {  // mode format T K E rows kdim: taken, row tiles, workgroups an XCD
+      int mode, fmt, T, K, E, rows, kdim;
+      in >> mode >> fmt >> T >> K >> E >> rows >> kdim;
+      const int tiles = eldr::wide_tiles(eldr::FfnMode(mode), rows);
+      std::printf("%d %d %d\n", eldr::ffn_wide_pays(eldr::FfnMode(mode), eldr::WeightFmt(fmt), T, K, E, rows, kdim),
+                  tiles, eldr::wide_slots(tiles, T, K, E));
     } else {
       return 2;
     }

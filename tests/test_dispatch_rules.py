@@ -90,6 +90,26 @@ def test_one_wave_kernel(ask, shape, fmt, up, down):
     assert tuple(_slim(ask, DOWN, fmt, T, shape) for T in range(1, 6)) == down
 
 
+def _wide(ask, mode, fmt, T, shape):
+    K, E, H, I = shape
+    return ask([("wide", mode, fmt, T, K, E, *_rows(mode, H, I))])[0]
+
+
+def test_wide_kernel_has_a_workgroup_for_each_item_a_round_holds(ask):
+    # even buckets of every size, cut to any group the device may choose: there is a
+    # workgroup for each of an XCD's items up to the 64 workgroups it holds at once
+    for shape, T in [((3, 37, 1056, 544), 1000), (QWEN, 300), (QWEN, 4096), (GPT_OSS, 256), (FEW_LARGE, 200),
+                     ((2, 16, 256, 128), 4096), ((1, 1, 32, 32), 65)]:
+        K, E, H, I = shape
+        for mode in (UP, DOWN):
+            _, tiles, slots = _wide(ask, mode, MXFP4, T, shape)
+            for U in range(K, E + 1):
+                bucket = -(-T * K // U)
+                for cap in (128, 64, 32):
+                    items = -(-tiles * U * -(-bucket // cap) // 8)
+                    assert slots >= min(items, 64), (shape, T, mode, U, cap, items, slots)
+
+
 def _cases(test):
     """The parameter sets of a parametrised test."""
     return next(m.args[1] for m in test.pytestmark if m.name == "parametrize")
