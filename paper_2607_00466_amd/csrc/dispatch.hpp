@@ -136,20 +136,75 @@ inline int wide_tiles(FfnMode mode, int rows) { return mode == kUp ? (rows + 127
 // Whether the wide kernel runs a projection of a batch of T > 64 tokens.  Its
 // items are twice as long as the small-batch kernel's, so there must be enough
 // of them to give every CU one: with E experts and T K / 128 further token
-// groups about 300 (measured: 312 items +4%, 330 items +15%, but 280 items
-// -6% and 171 items -14%).  With bf16 weights the buckets must also be large
-// enough for the MFMAs to show: 20 tokens on average for the up projection (25
-// tokens +6%; 16 tokens even, 18% with 64 of 128 experts active; 18.5 tokens
-// -1%; 12.5 tokens of one domain -2%) and 12 for the down projection, which
-// gains from staging h in whole lines (12.5 tokens +1%, of one domain +6%; 8
-// tokens -2%); 32 where the reduction is short and an item's start weighs more
-// (256 values: 9 and 16 tokens -6% and -7%, 62 tokens +14%).  MXFP4 streams a
-// quarter of the bytes and gains earlier, from 4 tokens (gpt-oss shape: T =
-// 128 +5%, 256 +3%, and +7% and +22% where 32 experts are active; at T = 80,
-// 2.5 tokens, with 4 experts active -5%).
+// groups about 310 (measured: 312 items +4%, 330 items +15%, but 300 items of
+// a ragged shape -4 to -13%, 280 items -6% and 171 items -14%).
+//
+// With bf16 weights the buckets must also be large enough for the MFMAs to
+// show: 20 tokens on average for the up projection (25 tokens +6%; 16 tokens
+// even; 18.5 tokens -1%; 12.5 tokens of one domain -2%) and 12 for the down
+// projection, which gains from staging h in whole lines (12.5 tokens +1%, of
+// one domain +6%; 8 tokens -2%); 32 where the reduction is short and an item's
+// start weighs more (256 values: 9 and 16 tokens -6% and -7%, 62 tokens +14%).
+//
+// MXFP4 streams a quarter of the bytes and gains earlier.  Over eight shapes
+// and six kinds of routing (uniform over all, 64, 32, 16 and top-k experts, and
+// skewed): up from 4 tokens (4 to 12 tokens +4% in the mean, 12 to 32 +9%, more
+// +20%); down from 8, below which it is even, and with fewer than 600 items
+// from 32 (60 experts of I = 1408, 496 to 576 items: -1 to -30%).
 inline bool ffn_wide_pays(FfnMode mode, WeightFmt fmt, int T, int K, int E, int rows, int kdim) {
   const long long items = (long long)wide_tiles(mode, rows) * (E + T * K / kWideTokens);
-  return T > 64 && items >= 300 && T * K >= (fmt == kMxfp4 ? 4 : kdim < 512 ? 32 : mode == kUp ? 20 : 12) * E;
+  if (T <= 64 || items < 310) return false;
+  if (fmt == kMxfp4) return T * K >= (mode == kUp ? 4 : items < 600 ? 32 : 8) * E;
+  return T * K >= (kdim < 512 ? 32 : mode == kUp ? 20 : 12) * E;
+}
+
+// The tokens of an item: 128, 64 or 32.  The host sees the batch, not the union,
+// so the device decides, from the union's buckets cut to `cap` tokens: `groups`
+// in all, t16 the buckets' 16-token tiles, cmax the largest bucket; an expert has
+// `tiles` row bands.  The largest cap is taken for which wide_cap_fits.
+//
+// bf16: an item is bound by its weights, which every group reads again, so
+// groups are cut only while there would not be an item for each CU: below 256
+// (400 tokens in 8 Qwen3 experts, up: 192 items of 128 tokens 64 us, 336 of 64
+// tokens 56), and to 32 only below 160 (60 experts of I = 1408, 256 tokens in 16,
+// down: 28 us with 64-token groups, 38 with 32).
+//
+// MXFP4: an item is bound by its products, so the longest one counts.  An item
+// costs about 3 tiles for its start and weights and 1 for each token tile.
+// Groups are cut while there are fewer items than CUs, or so few more (up to 352)
+// that a CU with two works while most have ended (gpt-oss shape, 256 tokens in 16
+// experts, down: 288 items 66 us, 480 items 49); and, where buckets are uneven,
+// while the longest item takes longer than a 512th of all the work, which the 512
+// resident workgroups would otherwise wait for (64 experts of H = 4096, I = 1024,
+// 80 tokens with skewed picks, up: 108 -> 74 us).  Even buckets gain nothing from
+// more, shorter items (256 tokens in 64 Qwen3 experts, up: 42 us, 53 cut to 32).
+constexpr int kWideStart = 3;
+constexpr int wide_longest(int cap, int cmax) {
+  const int groups = cmax > cap ? (cmax + cap - 1) / cap : 1;
+  return kWideStart + ((cmax + 15) / 16 + groups - 1) / groups;
+}
+// The longest item within a quarter of the mean one.
+constexpr bool wide_even(int cap, int groups, int t16, int cmax) {
+  return 4 * wide_longest(cap, cmax) * groups <= 5 * (kWideStart * groups + t16);
+}
+constexpr bool wide_cap_fits(WeightFmt fmt, int cap, int tiles, int groups, int t16, int cmax) {
+  const int items = tiles * groups;
+  if (cap <= 32) return true;
+  if (fmt == kBf16) return items >= (cap > 64 ? 256 : 160);
+  if (items < 256 || (items > 256 && items < 352)) return false;
+  return wide_even(cap, groups, t16, cmax) ||
+         tiles * (kWideStart * groups + t16) >= 512 * wide_longest(cap, cmax);
+}
+
+// Whether whole experts go round-robin over the XCDs, so that an expert's
+// activations are fetched into one XCD's L2, instead of the union's (expert, row
+// band) units, which balance the XCDs: while every bucket is one item's, and for
+// MXFP4 only if the buckets are even and the U experts divide evenly (within a
+// quarter) among the XCDs (8 experts of I = 14336, 66 tokens with skewed picks,
+// up: 182 us whole, 123 by bands).
+constexpr bool wide_whole(WeightFmt fmt, int cap, int groups, int t16, int cmax, int U) {
+  if (cmax > cap) return false;
+  return fmt == kBf16 || (wide_even(cap, groups, t16, cmax) && (U + kNumXcd - 1) / kNumXcd * kNumXcd * 4 <= 5 * U);
 }
 
 // Workgroups of the wide kernel an XCD: an expert's bands for its share of E

@@ -35,12 +35,6 @@
 namespace eldr {
 
 constexpr int kWideThreads = 256;  // 4 waves
-// Items below which token groups are cut smaller: one for each CU.  The host
-// sees the batch, not the union: where locality leaves few experts, 128-token
-// items would leave CUs idle (MXFP4, gpt-oss shape, T = 278 in 5 experts:
-// 183 -> 142 us; 300 tokens in 12 Qwen3 experts: 101 -> 97), while a bound of
-// 512 cut groups that did not need it (T = 300 in 32 experts: 108 -> 127).
-constexpr int kWideFill = 256;
 constexpr int kWideBuf = 32768;    // bytes of one staging buffer: 16 fragment pairs of 2 KB
 
 // One item: expert e's wave slots from 8 tile on by the c tokens (1 .. 16 NTB)
@@ -287,17 +281,20 @@ void ffn_wide_kernel(FfnArgs a) {
   const int slot = blockIdx.x / kNumXcd;
   const int slots = gridDim.x / kNumXcd;
   UnionLanes L = load_union(a);
-  // Tokens an item takes at most: 128, or 64 or 32 where the union's buckets
-  // would make fewer than kWideFill items of that size.
-  int cap = kWideTokens;
-  for (; cap > 32; cap /= 2) {
-    int n = 0;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) n += (L.c[j] + cap - 1) / cap;
-    if (a.tiles * __builtin_amdgcn_readlane(wave_inclusive_sum(n), kWave - 1) >= kWideFill) break;
-  }
-  // Whole experts are dealt while every bucket is one item's, else bands.
-  const bool whole = union_max(L) <= cap;
+  // Tokens an item takes at most, and how the items are dealt.
+  constexpr WeightFmt fmt = WeightFmt(FMT);
+  const int cmax = union_max(L);
+  auto total_of = [&](auto part) {
+    return __builtin_amdgcn_readlane(wave_inclusive_sum(part(L.c[0]) + part(L.c[1]) + part(L.c[2]) + part(L.c[3])),
+                                     kWave - 1);
+  };
+  const int t16 = FMT == kMxfp4 ? total_of([](const int c) { return (c + 15) / 16; }) : 0;
+  int cap = 2 * kWideTokens, n;
+  do {
+    cap /= 2;
+    n = total_of([cap](const int c) { return (c + cap - 1) / cap; });
+  } while (!wide_cap_fits(fmt, cap, a.tiles, n, t16, cmax));
+  const bool whole = wide_whole(fmt, cap, n, t16, cmax, L.U);
   auto groups = [cap](const int c) { return (c + cap - 1) / cap; };
   UnionEntry x{0, 0, 0};
   int total = slot + 1;

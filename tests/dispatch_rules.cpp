@@ -5,6 +5,7 @@
 #include <iostream>
 #include <sstream>
 #include <string>
+#include <vector>
 
 #include "dispatch.hpp"
 
@@ -34,6 +35,19 @@ int main() {
       const int tiles = eldr::wide_tiles(eldr::FfnMode(mode), rows);
       std::printf("%d %d %d\n", eldr::ffn_wide_pays(eldr::FfnMode(mode), eldr::WeightFmt(fmt), T, K, E, rows, kdim),
                   tiles, eldr::wide_slots(tiles, T, K, E));
+    } else if (what == "groups") {  // format row-tiles, then the union's buckets: cap, whole experts, groups
+      int fmt, tiles, c, cap = 2 * eldr::kWideTokens, n = 0, t16 = 0, cmax = 0;
+      std::vector<int> buckets;
+      in >> fmt >> tiles;
+      while (in >> c) buckets.push_back(c);
+      in.clear();
+      for (const int b : buckets) t16 += (b + 15) / 16, cmax = std::max(cmax, b);
+      do {
+        cap /= 2;
+        n = 0;
+        for (const int b : buckets) n += (b + cap - 1) / cap;
+      } while (!eldr::wide_cap_fits(eldr::WeightFmt(fmt), cap, tiles, n, t16, cmax));
+      std::printf("%d %d %d\n", cap, eldr::wide_whole(eldr::WeightFmt(fmt), cap, n, t16, cmax, (int)buckets.size()), n);
     } else {
       return 2;
     }

@@ -110,6 +110,53 @@ def test_wide_kernel_has_a_workgroup_for_each_item_a_round_holds(ask):
                     assert slots >= min(items, 64), (shape, T, mode, U, cap, items, slots)
 
 
+@pytest.mark.parametrize("shape,fmt,up,down", [
+    # the first batch of each projection the wide kernel takes
+    (QWEN, BF16, 320, 192), (QWEN, MXFP4, 65, 128),
+    (GPT_OSS, BF16, 640, 384), (GPT_OSS, MXFP4, 128, 256),
+    ((4, 60, 2048, 1408), BF16, 300, 180), ((4, 60, 2048, 1408), MXFP4, 65, 480),
+    ((3, 37, 1056, 544), BF16, 1067, 1067), ((8, 256, 2048, 256), BF16, 640, 1024),
+    ((2, 16, 256, 128), BF16, None, None), ((2, 16, 256, 128), MXFP4, None, None),
+])
+def test_wide_kernel(ask, shape, fmt, up, down):
+    for mode, first in ((UP, up), (DOWN, down)):
+        took = [_wide(ask, mode, fmt, T, shape)[0] for T in (1, 64)]
+        assert took == [0, 0]
+        if first is None:
+            assert _wide(ask, mode, fmt, 4096, shape)[0] == 0
+        else:
+            assert [_wide(ask, mode, fmt, T, shape)[0] for T in (first - 1, first, 2 * first)] == [0, 1, 1], mode
+
+
+def _groups(ask, fmt, tiles, buckets):
+    return ask([("groups", fmt, tiles, *buckets)])[0]
+
+
+def test_wide_groups(ask):
+    # even buckets that give a CU an item or two stay whole
+    assert _groups(ask, BF16, 6, [75] * 32 + [60] * 20) == [128, 1, 52]
+    assert _groups(ask, MXFP4, 6, [32] * 64) == [128, 1, 64]
+    # fewer items than CUs: cut, bf16 to 32 only below 160 items
+    assert _groups(ask, BF16, 6, [100] * 32) == [64, 0, 64]
+    assert _groups(ask, BF16, 8, [60] * 16) == [32, 0, 32]
+    assert _groups(ask, BF16, 8, [60] * 20) == [64, 1, 20]
+    # a few items more than CUs: MXFP4 is cut
+    assert _groups(ask, MXFP4, 12, [60] * 8 + [68] * 8)[0] == 32
+    assert _groups(ask, MXFP4, 8, [40] * 32) == [128, 1, 32]
+    # one bucket much longer than the others: MXFP4 is cut to it, and bands are dealt
+    skewed = [80, 40, 24] + [6] * 56
+    assert _groups(ask, MXFP4, 8, skewed)[:2] == [32, 0]
+    assert _groups(ask, BF16, 8, skewed)[:2] == [128, 1]
+    # but not where the work of many rounds hides it
+    assert _groups(ask, MXFP4, 128, skewed)[0] == 128
+    # experts that don't divide among the XCDs are not dealt whole
+    assert _groups(ask, MXFP4, 112, [40] * 8)[:2] == [128, 1]
+    assert _groups(ask, MXFP4, 112, [40] * 9)[:2] == [128, 0]
+    # an empty union, and the largest one
+    assert _groups(ask, MXFP4, 1, []) == [32, 1, 0]
+    assert _groups(ask, MXFP4, 128, [256] * 256)[0] == 128
+
+
 def _cases(test):
     """The parameter sets of a parametrised test."""
     return next(m.args[1] for m in test.pytestmark if m.name == "parametrize")
@@ -121,3 +168,12 @@ def test_the_one_wave_tests_run_that_kernel(ask):
         shape, f = (5, 40, H, I), BF16 if fmt == "bf16" else MXFP4
         assert [_slim(ask, UP, f, T, shape) for T in (1, 2, 3, 4, 8)] == [1, 1, 1, 1, 0], (fmt, H, I)
         assert [_slim(ask, DOWN, f, T, shape) for T in (1, 2, 3, 8)] == [1, 1, 1, 0], (fmt, H, I)
+
+
+def test_the_wide_tests_run_that_kernel(ask):
+    from tests import test_gpu_ffn_wide as W
+    for fmt, H, I in _cases(W.test_bucket_sizes_around_every_tile) + _cases(W.test_few_active_experts_take_smaller_groups):
+        f = BF16 if fmt == "bf16" else MXFP4
+        for mode in (UP, DOWN):
+            assert _wide(ask, mode, f, 2080, (4, 248, H, I))[0] == 1, (fmt, H, I, mode)
+            assert _wide(ask, mode, f, 64, (4, 248, H, I))[0] == 0
