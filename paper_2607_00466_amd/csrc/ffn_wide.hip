@@ -9,7 +9,8 @@
 //
 // * An item is 256 weight rows (up: 128 of W1 and the same of W3; down: of W2)
 //   by up to 128 tokens of one expert; each of its 4 waves owns four 16-row
-//   tiles, so a fragment read feeds four row tiles and the LDS is half idle.
+//   tiles, so a fragment read feeds four row tiles (the LDS is busy a fifth of the
+//   time).
 //   Two workgroups share a CU: 128 accumulator registers of the 256 a lane
 //   has, and 70 KB of LDS each.
 // * Weights go from memory to registers, as fragments, a ring of k-steps
@@ -26,10 +27,11 @@
 // * A slot's products are added in the same order as in every other kernel of
 //   the expert FFN, so its result is the same bits.
 //
-// Measured (Qwen3-30B-A3B shape, bf16, up + down, small-batch kernel -> this
-// one): T = 4096 898 -> 705 us (the up products 710 -> 935 TFLOP/s), T = 1000
-// 333 -> 283, T = 512 273 -> 250, T = 256 with 64 experts active 146 -> 123;
-// gpt-oss shape, MXFP4: T = 2048 1064 -> 845 us, T = 1024 686 -> 563.
+// Measured (up + down by the rules that choose the kernels, before it -> with it;
+// picks uniform over the experts named): Qwen3-30B-A3B shape, bf16, T = 4096 884
+// -> 691 us (the up products 709 -> 949 TFLOP/s), T = 1000 303 -> 260, T = 512
+// 245 -> 226, T = 256 in 64 experts (down alone takes it) 131 -> 126; gpt-oss
+// shape, MXFP4: T = 2048 1070 -> 857 us, T = 1000 660 -> 541, T = 256 341 -> 335.
 #include "ffn_wide.hpp"
 
 namespace eldr {
@@ -284,15 +286,15 @@ void ffn_wide_kernel(FfnArgs a) {
   // Tokens an item takes at most, and how the items are dealt.
   constexpr WeightFmt fmt = WeightFmt(FMT);
   const int cmax = union_max(L);
-  auto total_of = [&](auto part) {
-    return __builtin_amdgcn_readlane(wave_inclusive_sum(part(L.c[0]) + part(L.c[1]) + part(L.c[2]) + part(L.c[3])),
-                                     kWave - 1);
-  };
-  const int t16 = FMT == kMxfp4 ? total_of([](const int c) { return (c + 15) / 16; }) : 0;
-  int cap = 2 * kWideTokens, n;
-  do {
+  int cap = 2 * kWideTokens, n, t16;
+  do {  // the union's groups and, above them, its 16-token tiles (both below 2^13), in one sum
     cap /= 2;
-    n = total_of([cap](const int c) { return (c + cap - 1) / cap; });
+    int part = 0;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) part += (L.c[j] + cap - 1) / cap + ((L.c[j] + 15) / 16 << 16);
+    const int sum = __builtin_amdgcn_readlane(wave_inclusive_sum(part), kWave - 1);
+    n = sum & 0xffff;
+    t16 = sum >> 16;
   } while (!wide_cap_fits(fmt, cap, a.tiles, n, t16, cmax));
   const bool whole = wide_whole(fmt, cap, n, t16, cmax, L.U);
   auto groups = [cap](const int c) { return (c + cap - 1) / cap; };
