@@ -69,7 +69,9 @@ def _all_paths(layer: G.Layer, routing):
     for path in PATHS:
         _poison(buf)
         if path == "combined":
-            ids, w = B._gate(layer.x, layer.wg, d, buf, r, None)
+            if r is None:
+                B.moe_gate_topk(layer.x, layer.wg, d, buf.logits, buf.topk_ids, buf.topk_w)
+            ids, w = r or (buf.topk_ids, buf.topk_w)
             B.moe_bucket(ids, d, buf.counts, buf.offsets, buf.perm_token, buf.pair_pos,
                          buf.union_ids, buf.union_size)
             B.moe_expert_ffn(layer.x, layer.p13, layer.p2, buf.offsets, buf.perm_token,
@@ -212,7 +214,8 @@ def test_fused_entry_point_checks():
     G.say("case: one-launch FFN argument checks, tiny shape")
     layer = G.Layer(TINY, 4, seed=5, experts_on_host=False)
     d, buf = layer.d, layer.buf
-    ids, w = B._gate(layer.x, layer.wg, d, buf, None, None)
+    B.moe_gate_topk(layer.x, layer.wg, d, buf.logits, buf.topk_ids, buf.topk_w)
+    ids = buf.topk_ids
     lib = B.load()
     args = [B._ptr(layer.x), B._ptr(layer.p13), B._ptr(layer.p2), B._ptr(ids), d,
             B._ptr(buf.counts), B._ptr(buf.offsets), B._ptr(buf.perm_token), B._ptr(buf.pair_pos),
