@@ -177,3 +177,16 @@ def test_the_wide_tests_run_that_kernel(ask):
         for mode in (UP, DOWN):
             assert _wide(ask, mode, f, 2080, (4, 248, H, I))[0] == 1, (fmt, H, I, mode)
             assert _wide(ask, mode, f, 64, (4, 248, H, I))[0] == 0
+
+
+def test_the_choice_tests_run_the_kernels_they_name(ask):
+    from tests import test_gpu_kernel_choice as C
+    for fmt, E, K, H, I, T in C.SLIM + C.WIDE + C.MIXED:
+        f = BF16 if fmt == "bf16" else MXFP4
+        slim = [_slim(ask, mode, f, T, (K, E, H, I)) for mode in (UP, DOWN)]
+        wide = [_wide(ask, mode, f, T, (K, E, H, I))[0] for mode in (UP, DOWN)]
+        assert slim == ([1, 1] if T < 5 else [0, 0]), (fmt, T)
+        assert wide == ([0, 0] if T < 5 else [0, 1] if T == 256 else [1, 1]), (fmt, T)
+    for fmt, E, K, H, I, T in C.WIDE:
+        assert ask([("bucket", T, E, K, 0), ("gate", T, E, H)])[0][:2] == [1, 5]
+        assert ask([("gate", T, E, H)])[0] == [8, 1]
