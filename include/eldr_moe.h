@@ -121,8 +121,8 @@ int moe_gate_topk(const float* x, const float* w_gate, moe_dims d, float* logits
  * If an id is out of range or repeated within a token, union_size is set to
  * -1 and the other outputs are unspecified; moe_expert_ffn then does nothing.
  * Requires E * ceil(T / 32) <= 16384 (per-expert token bitmaps in LDS),
- * else MOE_ERR_UNSUPPORTED; above 8192 it raises the kernel's dynamic LDS
- * limit on the current device first (MOE_ERR_HIP if the runtime refuses).
+ * else MOE_ERR_UNSUPPORTED; from about 10,200 it raises the kernel's dynamic
+ * LDS limit on the current device first (MOE_ERR_HIP if the runtime refuses).
  */
 int moe_bucket(const int32_t* topk_ids, moe_dims d, int32_t* counts, int32_t* offsets,
                int32_t* perm_token, int32_t* pair_pos, int32_t* union_ids,
@@ -171,13 +171,15 @@ size_t moe_ffn_workspace_bytes(moe_dims d);
  * s in [offsets[e], offsets[e+1]) holding token t = perm_token[s]:
  *   y_perm[s, :] = W2_e (silu(W1_e x[t]) * (W3_e x[t]))
  * Each active expert's weights are streamed from HBM once per call when its
- * bucket fits one token group: the whole batch when T <= 64, else 128
- * tokens (64 or 32 where larger groups would leave CUs without work); a
+ * bucket fits one token group: the whole batch when T <= 64, else 128 tokens
+ * (64 or 32 in large batches whose union would leave CUs without work).  A
  * bigger bucket is split into groups whose workgroups run side by side on one
- * XCD and share that XCD's L2 for the repeated weight reads.  Experts outside the union are never touched.
- * Work follows the union's dispatch order (largest buckets first): with
- * T <= 64 experts are dealt round-robin over the 8 XCDs, with T > 64 their
- * (expert, row band) units are, so skewed buckets still load the XCDs evenly.
+ * XCD and share that XCD's L2 for the repeated weight reads.  Experts outside
+ * the union are never touched.
+ * Work follows the union's dispatch order (largest buckets first).  Whole
+ * experts are dealt round-robin over the 8 XCDs with T <= 64, and above while
+ * every bucket fits one token group; else their (expert, row band) units are,
+ * so skewed buckets still load the XCDs evenly.
  * The grid is sized from E and T alone and reads union_size on the device,
  * so no host synchronisation is needed between moe_bucket and this call.
  *
@@ -353,9 +355,10 @@ int moe_pack_mxfp4_down(const uint8_t* w2_codes, const uint8_t* w2_scales, int32
  * registers (exact: an E2M1 value times a power of two in range is a bf16
  * number) and multiplied exactly as in moe_expert_ffn, so the result equals
  * moe_expert_ffn's on the dequantized weights.  Each active expert's codes
- * and scales are streamed once per call when its bucket fits one token group
- * (the whole batch when T <= 64, else 32 to 128 tokens by the batch's size); a
- * bigger bucket is split into groups sharing the XCD's L2.
+ * and scales are streamed once per call when its bucket fits one token group:
+ * the whole batch when T <= 64, else 32 tokens, or in batches large enough
+ * 128, 64 or 32 by the union's buckets.  A bigger bucket is split into groups
+ * sharing the XCD's L2.
  * Other arguments, the workspace (moe_ffn_workspace_bytes) and the error
  * behaviour are those of moe_expert_ffn; in addition H % 64 == 0 and
  * I % 64 == 0 (else MOE_ERR_UNSUPPORTED), and the scale pointers must be

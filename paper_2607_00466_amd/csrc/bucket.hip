@@ -240,10 +240,10 @@ extern "C" int moe_bucket(const int32_t* topk_ids, moe_dims d, int32_t* counts, 
   const eldr::BucketLaunch l = eldr::bucket_launch(d.T, d.E, d.K, in_place);
   const auto kernel = l.large ? (in_place ? eldr::bucket_kernel<true, true> : eldr::bucket_kernel<true, false>)
                               : (in_place ? eldr::bucket_kernel<false, true> : eldr::bucket_kernel<false, false>);
-  // Bitmaps above 64 KiB (about 8192 words) need the kernel's dynamic LDS
-  // limit raised, on the current device, before the launch; the call is cheap
-  // and shapes that need it are prefill-sized, so it is made on every such
-  // call rather than cached.
+  // Above 64 KiB (bitmaps, prefixes and tables: from about 10,200 bitmap words)
+  // the kernel's dynamic LDS limit has to be raised, on the current device,
+  // before the launch; the call is cheap and shapes that need it are
+  // prefill-sized, so it is made on every such call rather than cached.
   if (l.lds > 64 * 1024 && hipFuncSetAttribute(reinterpret_cast<const void*>(kernel),
                                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)l.lds) != hipSuccess)
     return MOE_ERR_HIP;

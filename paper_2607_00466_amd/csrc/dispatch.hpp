@@ -15,7 +15,7 @@ constexpr int kNumXcd = 8;  // MI355X: 8 XCDs, workgroups dispatched round-robin
 
 // ----------------------------------------------------------------- moe_bucket
 
-constexpr int kBucketMaxWords = 16384;  // E * ceil(T / 32) limit
+constexpr int kBucketMaxWords = 16384;  // E * ceil(T / 32) limit (without the odd stride)
 constexpr int kBucketSmall = 256;       // tokens, and
 constexpr int kBucketFew = 3072;        // pairs, of a batch counted by one thread an expert
 constexpr int kBucketPairs = 2048;      // pairs a workgroup writes: two a thread
@@ -30,6 +30,8 @@ constexpr size_t bucket_lds_bytes(int T, int E) {
   const size_t EW = (size_t)E * bucket_stride(T);
   return EW * 4 + ((EW + 1) & ~(size_t)1) * 2 + (size_t)E * 4 * 4;
 }
+
+static_assert(bucket_lds_bytes(2048, 256) == 103936, "the most that the limits admit: 104 KB");
 
 struct BucketLaunch {
   bool large;  // several threads an expert

@@ -18,9 +18,10 @@
 //   workgroup, which has no item, writes moe_bucket's outputs.
 // * The products are added in the other kernels' order: the same bits.
 //
-// Measured (up + down, four-wave items -> this): Qwen3-30B-A3B shape T = 1
-// 26.4 -> 19.9 us, T = 3 49.8 -> 44.4; gpt-oss shape MXFP4 T = 1 37.4 -> 30.2,
-// T = 4 53.5 -> 45.9, bf16 T = 1 64.4 -> 52.7.
+// Measured (up + down by the rules that choose the kernels, four-wave items ->
+// with it; random experts): Qwen3-30B-A3B shape T = 1 28.6 -> 18.8 us, T = 3 (up
+// alone takes it) 48.7 -> 42.4; gpt-oss shape MXFP4 T = 1 35.7 -> 29.1, T = 4 50.6
+// -> 44.5, bf16 T = 1 71.4 -> 59.4.
 #include "ffn_slim.hpp"
 
 namespace eldr {
