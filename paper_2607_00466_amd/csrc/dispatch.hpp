@@ -148,7 +148,7 @@ inline int wide_tiles(FfnMode mode, int rows) { return mode == kUp ? (rows + 127
 // one domain +6%; 8 tokens -2%); 32 where the reduction is short and an item's
 // start weighs more (256 values: 9 and 16 tokens -6% and -7%, 62 tokens +14%).
 //
-// MXFP4 streams a quarter of the bytes and gains earlier.  Over eight shapes
+// MXFP4 streams a quarter of the bytes and gains earlier.  Over six shapes
 // and six kinds of routing (uniform over all, 64, 32, 16 and top-k experts, and
 // skewed): up from 4 tokens (4 to 12 tokens +4% in the mean, 12 to 32 +9%, more
 // +20%); down from 8, below which it is even, and with fewer than 600 items
