@@ -109,8 +109,9 @@ int moe_gate_topk(const float* x, const float* w_gate, moe_dims d, float* logits
  *   perm_token [T*K]   token of each slot: experts ascending, and within an
  *                      expert tokens ascending
  *   pair_pos   [T*K]   pair_pos[t*K + j] = slot of (t, topk_ids[t, j]); it may
- *                      be topk_ids itself (moe_bucket alone: the calls that
- *                      take the routing and run the FFN read it on)
+ *                      be topk_ids itself (here only: in the calls that build
+ *                      the buckets and run the FFN, workgroups still read
+ *                      the routing while others write)
  *   union_ids  [2E]    the union twice: [0, E) the experts with counts > 0
  *                      ascending, then -1 padding; [E, 2E) the same experts
  *                      in dispatch order -- more 16-token tiles
